@@ -1,0 +1,291 @@
+// Box stencils of radius 2..4 in 3D on the FP32 matrix cores (gfx950).
+//
+//     out(p) = sum over offsets k in [-r, r]^3 of w[k] * u(p + k)
+//
+// A box of radius r costs (2r+1)^3 multiply-adds per point, so these kernels
+// are bound by arithmetic, not by memory.  What one SIMD of this chip issues
+// (measured, independent chains, all CUs): v_fmac_f32 with a weight in a
+// scalar register 76 TFLOP/s, with all operands in vector registers 105,
+// v_mfma_f32_4x4x1_16b_f32 141.  The last one, with the A block broadcast to
+// all 16 blocks (CBSZ = 4, ABID = b), is
+//     D[i] (lane l) += A[block b, row i] * B (lane l),   i = 0..3,
+// four multiply-adds per lane with one input value per lane and four weights
+// that every lane shares: the shape of a stencil that streams along z and
+// adds each input plane to the 2r+1 output planes it touches.  Four of those
+// planes are the four rows of D; the lanes keep the points they would own in
+// a vector kernel; and one VGPR holds 16 such groups of four weights (the A
+// blocks), so the whole weight set of the largest box stays in 16 VGPRs.
+// Each product is one fused multiply-add rounded to nearest even (compared
+// bit for bit with fmaf, denormals and infinities included), and each output
+// adds its terms in the order the vector kernel did.
+//
+// A workgroup owns a TX x 2*(rows per block) tile and streams along z.  A
+// lane owns 4 consecutive x points of 2 adjacent rows.  Each input plane (the
+// tile plus an r-row, 4-column frame) is staged once in a double-buffered LDS
+// plane; the loads of plane z+1 are in flight while plane z is computed.
+//
+// Measured against the vector kernel it replaced, same GPU, us per sweep:
+//     512^3        r = 2: 711 -> 415   r = 3: 1961 -> 854   r = 4: 4202 -> 1664
+//     384x320x256  r = 2: 405 -> 106   r = 3: 1040 -> 219   r = 4: 2258 ->  433
+// (r = 3, 512^3: 108 TFLOP/s; r = 4: 118.)  What is left at r = 3 and 4 is the
+// matrix rate, one unused row in eight at r = 3; at r = 2 a plane's staging,
+// stores and register moves weigh as much as half of its MFMA instructions.
+//
+// The 2r+1 accumulators of a point, k = 0 (oldest output plane, z - r) to 2r:
+//   r = 3: 7 = groups {0..3} and {4..6, unused};
+//   r = 2, 4: 2r full ones in r/2 groups, and one left over; the left-over
+//     accumulators of a lane's two rows share one group, for the input rows
+//     that reach both outputs (all but the first and the last, which add to
+//     one output each with a vector multiply-add).  No group ever multiplies
+//     an input by a zero weight into an accumulator that is read, so an
+//     infinity or a NaN reaches exactly the points whose box holds it.
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include <algorithm>
+#include <type_traits>
+
+#include "internal.h"
+#include "kcommon.h"
+
+namespace sp {
+
+namespace {
+
+struct TileB {
+    int tiles_x, tiles_y, zchunk;
+};
+
+template <int R> struct BoxW {
+    float w[(2 * R + 1) * (2 * R + 1) * (2 * R + 1)];
+};
+
+// c[i] += (weight i of group E) * b for i = 0..3; group E is block E % 16 of
+// register E / 16 of the packed weights.
+template <int E, int NV>
+__device__ __forceinline__ void mac4(f4v &c, const float (&a)[NV], float b) {
+    c = __builtin_amdgcn_mfma_f32_4x4x1f32(a[E / 16], b, c, 4, E % 16, 0);
+}
+
+template <int I, int N, typename F> __device__ __forceinline__ void static_for(F f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>());
+        static_for<I + 1, N>(f);
+    }
+}
+
+template <int R, int TX, int NT>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2)))
+k_box3(SuiteArgs a, TileB t, BoxW<R> W) {
+    constexpr int D = 2 * R + 1;
+    constexpr bool EXTRA = R % 2 == 0;           // a left-over accumulator (k = 2R)
+    constexpr int G = EXTRA ? R / 2 : (D + 3) / 4;
+    constexpr int LX = TX / 4, TY = 2 * (NT / LX);
+    constexpr int LC = LX + 2, LR = TY + 2 * R;  // LDS row: x0-4 .. x0+TX+3
+    constexpr int NCH = LR * LC, K = (NCH + NT - 1) / NT;
+    constexpr int NM = (D * D * G + 15) / 16;    // VGPRs of the full groups' weights
+    constexpr int NX = EXTRA ? (2 * R * D + 15) / 16 : 1;
+    __shared__ f4v lds[2][NCH];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int lx = tid % LX, ly = tid / LX;
+    int lin = xcd_tile(blockIdx.x, gridDim.x);
+    const int tx = lin % t.tiles_x;
+    lin /= t.tiles_x;
+    const int ty = lin % t.tiles_y;
+    const int zc = lin / t.tiles_y;
+    const int x0 = tx * TX, y0 = ty * TY;
+    const int zb = zc * t.zchunk, ze = min(zb + t.zchunk, a.nz);
+
+    // Pack the weights: lane 4 b + i of register n holds weight i of group
+    // 16 n + b.  Full groups: (tap, g) -> accumulators k = 4 g + i, which is
+    // offset dz = R - k.  Shared group of rows j = 0, 1: input row q (1 .. 2R
+    // of the lane's 2R+2) is offset dy = q - j - R, dz = -R.
+    float wm[NM], wx[NX];
+    const int wb = lane >> 2, wi = lane & 3;
+#pragma unroll
+    for (int n = 0; n < NM; ++n) {
+        const int e = n * 16 + wb, tap = e / G, k = 4 * (e % G) + wi;
+        const bool okw = tap < D * D && k < D;
+        wm[n] = okw ? W.w[(D - 1 - k) * D * D + tap] : 0.f;
+    }
+#pragma unroll
+    for (int n = 0; n < NX; ++n) {
+        const int e = n * 16 + wb, q = e / D + 1, dx = e % D;
+        const bool okw = EXTRA && q <= 2 * R && wi < 2;
+        wx[n] = okw ? W.w[(q - wi) * D + dx] : 0.f;
+    }
+
+    // This thread's chunks of every plane: in-plane element offsets (0 for a
+    // chunk outside the grid's frame, fetched from a valid address and
+    // replaced by zero).
+    int32_t off[K];
+    bool okc[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int c = tid + k * NT;
+        const int row = c / LC, col = c - row * LC;
+        const int gy = y0 - R + row, gx = x0 - 4 + 4 * col;
+        okc[k] = c < NCH && gy < a.ny + R && gx < a.nx + 4;
+        off[k] = okc[k] ? (int32_t)(gy * a.sy + gx) : 0;
+    }
+    f4v nxt[K];
+    auto fetch = [&](int zp) {
+        const float *p = a.u + (int64_t)zp * a.sz;
+#pragma unroll
+        for (int k = 0; k < K; ++k) nxt[k] = ld4(p + off[k]);
+    };
+    auto stage = [&](int b) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int c = tid + k * NT;
+            if (k + 1 < K || c < NCH) lds[b][c] = okc[k] ? nxt[k] : f4v{0.f, 0.f, 0.f, 0.f};
+        }
+    };
+
+    const f4v zero = {0.f, 0.f, 0.f, 0.f};
+    f4v acc[2][4][G], ax[4];                     // [row][point][group]; ax[point]: the rows' k = 2R
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        ax[i] = zero;
+#pragma unroll
+        for (int g = 0; g < G; ++g) acc[0][i][g] = acc[1][i][g] = zero;
+    }
+
+    // One input plane; G0, G1: the first / second group has an output plane
+    // inside this chunk (the chunk's first and last planes skip one).
+    auto plane = [&](const f4v *L, auto g0, auto g1) {
+        static_for<0, D + 1>([&](auto qc) {
+            constexpr int q = decltype(qc)::value;
+            const f4v *row = L + (2 * ly + q) * LC + lx;
+            const f4v l = row[0], c = row[1], r = row[2];
+            const float v[12] = {l.x, l.y, l.z, l.w, c.x, c.y, c.z, c.w, r.x, r.y, r.z, r.w};
+            static_for<0, D>([&](auto dc) {
+                constexpr int dx = decltype(dc)::value;
+                static_for<0, 2>([&](auto jc) {
+                    constexpr int j = decltype(jc)::value, dy = q - j;
+                    if constexpr (dy >= 0 && dy < D) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            if constexpr (decltype(g0)::value)
+                                mac4<(dy * D + dx) * G>(acc[j][i][0], wm, v[4 + i + dx - R]);
+                            if constexpr (G > 1 && decltype(g1)::value)
+                                mac4<(dy * D + dx) * G + G - 1>(acc[j][i][G - 1], wm, v[4 + i + dx - R]);
+                        }
+                    }
+                });
+                if constexpr (EXTRA && q >= 1 && q <= 2 * R) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) mac4<(q - 1) * D + dx>(ax[i], wx, v[4 + i + dx - R]);
+                }
+            });
+            // input rows that reach one of the two outputs only
+            if constexpr (EXTRA && (q == 0 || q == 2 * R + 1)) {
+                constexpr int j = q == 0 ? 0 : 1;
+#pragma unroll
+                for (int dx = 0; dx < D; ++dx)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        ax[i][j] = fmaf(W.w[(q - j) * D + dx], v[4 + i + dx - R], ax[i][j]);
+            }
+        });
+    };
+
+    const int x = x0 + lx * 4, y = y0 + 2 * ly;
+    const int nst = a.nx - x;
+    fetch(zb - R);
+    stage(0);
+    lds_barrier();
+    for (int zp = zb - R; zp < ze + R; ++zp) {
+        const int b = (zp - zb + R) & 1;
+        const bool more = zp + 1 < ze + R;
+        if (more) fetch(zp + 1);
+        if (G == 1 || (zp >= zb + R - 3 && zp < ze + R - 4))
+            plane(lds[b], std::true_type(), std::true_type());
+        else if (zp < ze + R - 4)
+            plane(lds[b], std::false_type(), std::true_type());
+        else
+            plane(lds[b], std::true_type(), std::false_type());
+        const int zo = zp - R;
+        if (zo >= zb && nst > 0) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const f4v o = {acc[j][0][0][0], acc[j][1][0][0], acc[j][2][0][0], acc[j][3][0][0]};
+                if (y + j < a.ny) st_part(a.out + (int64_t)zo * a.sz + (int64_t)(y + j) * a.sy + x, o, nst);
+            }
+        }
+        // accumulator k takes over k+1, the newest starts at zero
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+#pragma unroll
+                for (int k = 0; k < D; ++k) {
+                    const float from = k + 1 == D ? 0.f
+                                       : (k + 1 < 4 * G) ? acc[j][i][(k + 1) / 4 % G][(k + 1) % 4]
+                                                         : ax[i][j];
+                    if (k < 4 * G) acc[j][i][k / 4 % G][k % 4] = from;
+                }
+            }
+            ax[i] = zero;
+        }
+        if (more) {
+            stage(b ^ 1);
+            lds_barrier();
+        }
+    }
+}
+
+template <int R, int TX>
+hipError_t run_box3(const float *w, const SuiteArgs &a, hipStream_t s) {
+    constexpr int NT = 256, TY = 2 * (NT / (TX / 4));
+    TileB t;
+    t.tiles_x = (a.nx + TX - 1) / TX;
+    t.tiles_y = (a.ny + TY - 1) / TY;
+    const int64_t tiles = (int64_t)t.tiles_x * t.tiles_y;
+    // z-split: a CU works through its blocks at a fixed rate, so the time is
+    // (blocks per CU, rounded up) x (planes per block: the chunk, and start-up
+    // planes worth about R + 1).  One block per CU (one wave per SIMD) leaves
+    // the LDS reads between two MFMA runs uncovered, 7 % at r = 2 and 3
+    // (384x320x256: 115 against 107 us and 225 against 216 with two blocks);
+    // at r = 4 the runs are long enough (434 against 452).
+    double best = -1.0;
+    t.zchunk = a.nz;
+    for (int k = 1; k <= std::min(a.nz, 1024); ++k) {
+        const int zc = (a.nz + k - 1) / k;
+        const int64_t per_cu = (tiles * ((a.nz + zc - 1) / zc) + 255) / 256;
+        const double cost = (double)per_cu * (zc + R + 1) * (per_cu == 1 && R < 4 ? 1.07 : 1.0);
+        if (best < 0 || cost < best) {
+            best = cost;
+            t.zchunk = zc;
+        }
+    }
+    const int64_t nblk = tiles * ((a.nz + t.zchunk - 1) / t.zchunk);
+    if (nblk > 0x7fffffff) return hipErrorInvalidValue;
+    BoxW<R> W;
+    std::copy(w, w + sizeof(W.w) / sizeof(float), W.w);
+    hipLaunchKernelGGL((k_box3<R, TX, NT>), dim3((unsigned)nblk), dim3(NT), 0, s, a, t, W);
+    return hipGetLastError();
+}
+
+// 64 x 32 or 128 x 16 tiles, whichever covers the plane with fewer (they run
+// alike per tile: 512^3 at r = 3 854 and 868 us); the squarer ones on a tie,
+// whose frame is the smaller.
+template <int R> hipError_t pick_box3(const float *w, const SuiteArgs &a, hipStream_t s) {
+    const int64_t t64 = (int64_t)((a.nx + 63) / 64) * ((a.ny + 31) / 32);
+    const int64_t t128 = (int64_t)((a.nx + 127) / 128) * ((a.ny + 15) / 16);
+    return t64 <= t128 ? run_box3<R, 64>(w, a, s) : run_box3<R, 128>(w, a, s);
+}
+
+}  // namespace
+
+hipError_t launch_box3(int radius, const float *w, const SuiteArgs &a, hipStream_t s) {
+    switch (radius) {
+        case 2: return pick_box3<2>(w, a, s);
+        case 3: return pick_box3<3>(w, a, s);
+        case 4: return pick_box3<4>(w, a, s);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace sp

@@ -194,6 +194,8 @@ struct SuiteArgs {
 // axes.  shape 0 = star, 1 = box.
 hipError_t launch_suite(int shape, int ndim, int radius, const float *w, const SuiteArgs &a,
                         hipStream_t s);
+// The 3D box of radius 2..4, w as above, on the FP32 matrix cores.
+hipError_t launch_box3(int radius, const float *w, const SuiteArgs &a, hipStream_t s);
 
 // eta = eta_max * sum over axes (d_a / width)^2 on every cell of the padded
 // extent, d_a = max(0, width - 1 - a, a - (n_a - width)).

@@ -12,8 +12,9 @@
 //    box and for the centre row of a star;
 //  * no LDS and no barriers: the four waves of a block are independent, and
 //    loads of row y+r+1 are in flight while row y is computed.
-// 3D (a workgroup = a 256 x TY tile streaming along z; the accumulating, or
-// semi-stencil, arrangement):
+// 3D stars and the box of radius 1 (larger boxes: box.hip): a workgroup = a
+// 256 x TY tile streaming along z (the accumulating, or
+// semi-stencil, arrangement);
 //  * each plane of the tile plus an r-row, 4-column frame (corners included)
 //    is fetched once into a double-buffered LDS slot, one barrier per plane;
 //  * the plane's contribution to the 2r+1 output planes it touches is added
@@ -315,9 +316,7 @@ hipError_t run2(const float *w, const SuiteArgs &a, hipStream_t s) {
 
 template <int R, bool BOX>
 hipError_t run3(const float *w, const SuiteArgs &a, hipStream_t s) {
-    // box kernels of radius >= 3 are long unrolled bodies: one row per thread
-    constexpr bool small = BOX && R >= 3;
-    constexpr int TY = small ? 8 : 16, RY = small ? 1 : 2;
+    constexpr int TY = 16, RY = 2;
     Tile3 t;
     t.tiles_x = (a.nx + 255) / 256;
     t.tiles_y = (a.ny + TY - 1) / TY;
@@ -348,11 +347,13 @@ hipError_t dispatch(int ndim, int radius, const float *w, const SuiteArgs &a, hi
             case 4: return run2<4, BOX>(w, a, s);
         }
     } else {
+        // a 3D box of radius 2 or more is bound by arithmetic: matrix cores
+        if constexpr (BOX) return radius == 1 ? run3<1, true>(w, a, s) : launch_box3(radius, w, a, s);
         switch (radius) {
-            case 1: return run3<1, BOX>(w, a, s);
-            case 2: return run3<2, BOX>(w, a, s);
-            case 3: return run3<3, BOX>(w, a, s);
-            case 4: return run3<4, BOX>(w, a, s);
+            case 1: return run3<1, false>(w, a, s);
+            case 2: return run3<2, false>(w, a, s);
+            case 3: return run3<3, false>(w, a, s);
+            case 4: return run3<4, false>(w, a, s);
         }
     }
     return hipErrorInvalidValue;
