@@ -122,7 +122,7 @@ hipError_t launch_inject_grad(const SweepArgs &a, const int32_t *xyz, int n, con
 // out = 2 G / v on the interior (FP32 grid layout for out, v; FP64 G).
 hipError_t launch_grad_finish(const double *G, const float *v, float *out, int64_t sy, int64_t sz,
                               int nx, int ny, int nz, hipStream_t s);
-// *out = sum of n partials, in index order.
+// *out = sum of n partials, in an order that n alone fixes.
 hipError_t launch_sum(const double *partial, int n, double *out, hipStream_t s);
 
 // Error reporting shared by the C-ABI translation units (thread-local message).
