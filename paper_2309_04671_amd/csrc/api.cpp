@@ -595,12 +595,10 @@ int sp_wave_step_pml(const sp_grid *g, const sp_coeffs *c, double dt, double dx,
         if (dec == SP_PML_TWO && mode == sp::MODE_PML) {
             // the shell as one launch of 512-thread blocks (one per CU):
             // the z and y slabs on 256x8x1 tiles, the x slabs on 32x64x1
+            // (their z-chunks: split_shell, once every slab is known)
             b.t.tx = wide ? 256 : 32;
             b.t.ty = wide ? 8 : 64;
             b.t.ry = 1;
-            b.t.zchunk = sp::occupancy_zchunk((int64_t)((b.a.nx + b.t.tx - 1) / b.t.tx) *
-                                                  ((b.a.ny + b.t.ty - 1) / b.t.ty),
-                                              b.a.nz, 256);
         }
         fill_tiling(b.a, b.t);
     };
@@ -616,6 +614,60 @@ int sp_wave_step_pml(const sp_grid *g, const sp_coeffs *c, double dt, double dx,
         add(0, W, W, ny - W, W, nz - W, sp::MODE_PML, false);
         add(xe, nx, W, ny - W, W, nz - W, sp::MODE_PML, false);
     }
+    // z-chunks of the shell's slabs: each slab split to fill the GPU by itself
+    // (l = 0), or at most l planes in the z and y slabs and 3/4 l in the x
+    // slabs, whichever launch ends first in a count of planes per CU.  All
+    // slabs share one launch, so what has to fill whole rounds of blocks is
+    // their total (alone, each slab of a mid-size grid had 14-plane blocks
+    // for 6 planes); and each XCD takes one contiguous eighth of the blocks,
+    // 32 at a time, so blocks of unlike cost leave XCDs idle.  A block's
+    // start-up costs about 6 planes, an x-slab plane 1.15 (two of each row's
+    // lines are neighbours').  Per step, before -> now: 448x384x256, W = 32:
+    // 310 -> 222 us; 250x230x200, W = 16: 79 -> 73; 300x700x333, W = 32: 571
+    // -> 398; 512^3, W = 16: 633 -> 589; 1024x1024x512, W = 32: 1967 both.
+    auto split_shell = [&] {
+        auto chunk = [&](const Box &b, int l) {
+            if (l == 0) return sp::occupancy_zchunk((int64_t)b.a.tiles_x * b.a.tiles_y, b.a.nz, 256);
+            const int most = b.wide ? l : 3 * l / 4, chunks = (b.a.nz + most - 1) / most;
+            return (b.a.nz + chunks - 1) / chunks;
+        };
+        double best = -1.0;
+        int best_l = 0;
+        for (int l = 0; l <= 64; l = l == 0 ? 4 : l + std::max(1, l / 10)) {
+            int64_t end[7] = {0};            // end[q]: first block after slab q
+            double cost[7];
+            for (int q = 1; q < nb; ++q) {
+                const Box &b = boxes[q];
+                const int zc = chunk(b, l);
+                end[q] = end[q - 1] + (int64_t)b.a.tiles_x * b.a.tiles_y * ((b.a.nz + zc - 1) / zc);
+                cost[q] = (zc + 6) * (b.wide ? 1.0 : 1.15);
+            }
+            const int64_t per = end[nb - 1] / 8, rest = end[nb - 1] % 8;
+            double longest = 0;
+            int64_t first = 0;
+            for (int x = 0; x < 8; ++x) {
+                const int64_t n = per + (x < rest), last = first + n;
+                double sum = 0, most = 0;
+                for (int q = 1; q < nb; ++q) {
+                    const int64_t k = std::min(last, end[q]) - std::max(first, end[q - 1]);
+                    if (k <= 0) continue;
+                    sum += (double)k * cost[q];
+                    most = std::max(most, cost[q]);
+                }
+                longest = std::max(longest, sum / 32 + most * ((double)((n + 31) / 32) - (double)n / 32));
+                first = last;
+            }
+            if (best < 0 || longest < 0.99 * best) {
+                best = longest;
+                best_l = l;
+            }
+        }
+        for (int q = 1; q < nb; ++q) {
+            boxes[q].t.zchunk = chunk(boxes[q], best_l);
+            fill_tiling(boxes[q].a, boxes[q].t);
+        }
+    };
+    if (dec == SP_PML_TWO) split_shell();
     const int nrec = rec ? rec->n : 0;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int64_t step0 = st->step;
