@@ -368,6 +368,30 @@ void step_args(SweepArgs &a, const sp_grid *g, void *cur, void *prev, void *out,
 
 using sp::prep_wave;
 
+namespace {
+
+// Row `row` of the traces: receivers `rec` (may be NULL) of the field whose
+// interior origin is `field`.
+sp::RecArgs rec_args(const sp_grid *g, const sp_receivers *rec, const void *field, const float *scale,
+                     int64_t row) {
+    sp::RecArgs r;
+    std::memset(&r, 0, sizeof r);
+    if (!rec || rec->n <= 0) return r;
+    r.field = field;
+    r.scale = scale;
+    r.xyz = rec->xyz;
+    r.traces = rec->traces + row * rec->trace_stride;
+    r.sy = g->pitch_x;
+    r.sz = g->pitch_x * g->pitch_y;
+    r.nx = g->nx;
+    r.ny = g->ny;
+    r.nz = g->nz;
+    r.n = rec->n;
+    return r;
+}
+
+}  // namespace
+
 extern "C" {
 
 int sp_wave_step(const sp_grid *g, const sp_coeffs *c, double dt, double dx, const sp_grid *gv,
@@ -388,23 +412,19 @@ int sp_wave_step(const sp_grid *g, const sp_coeffs *c, double dt, double dx, con
         return fail(SP_EINVAL, "sp_wave_step: v overlaps a wavefield");
     if (st->step < 0) return fail(SP_EINVAL, "sp_wave_step: negative step counter");
     const int nsrc = a.src.n;
-    const int nrec = rec ? rec->n : 0;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int64_t step0 = st->step;
-    const int64_t eb = g->elem_bytes;
-    const int nslab = (g->nz + SP_SLAB - 1) / SP_SLAB;
     float *meta = static_cast<float *>(st->meta);
-    auto slot_s = [&](int64_t k) { return meta + ((k % 4 + 4) % 4) * 2 * nslab; };
     for (int k = 0; k < nsteps; ++k) {
-        char *prev = static_cast<char *>(st->prev) + g->origin * eb;
         const int64_t n = st->step;
         sp::step_args(a, g, st->cur, st->prev, st->prev, meta, n, nsrc ? src->amp : nullptr,
                       nsrc ? src->amp_stride : 0);
+        // the sweep also records its input, the previous step's output; the
+        // last output has a launch of its own
+        a.rec = rec_args(g, k > 0 ? rec : nullptr, a.u, a.meta.s_u, n - 1 - step0);
         hipError_t err = sp::launch_sweep(sp::MODE_WAVE, g->dtype, t, a, s);
-        if (err == hipSuccess && nrec > 0)
-            err = sp::launch_record(g->dtype, prev, meta ? slot_s(n + 1) : nullptr, a.sy, a.sz,
-                                    g->nx, g->ny, g->nz, rec->xyz, nrec,
-                                    rec->traces + (st->step - step0) * rec->trace_stride, s);
+        if (err == hipSuccess && k + 1 == nsteps)
+            err = sp::launch_record(g->dtype, rec_args(g, rec, a.out, a.meta.s_out, n - step0), s);
         if (err != hipSuccess)
             return fail(SP_EDEVICE, "sp_wave_step: launch failed at step %lld: %s",
                         (long long)st->step, hipGetErrorString(err));
@@ -466,7 +486,6 @@ int sp_wave_step_fused(const sp_grid *g, const sp_coeffs *c, double dt, double d
     b.nzc = (g->nz + tb.zchunk - 1) / tb.zchunk;
 
     const int nsrc = a.src.n;
-    const int nrec = rec ? rec->n : 0;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int64_t step0 = st->step;
     const int64_t org = g->origin;
@@ -482,10 +501,8 @@ int sp_wave_step_fused(const sp_grid *g, const sp_coeffs *c, double dt, double d
             b.amp1 = src->amp + (n + 1) * src->amp_stride;
         }
         hipError_t err = sp::launch_tb2(tb, b, s);
-        for (int h = 0; h < 2 && err == hipSuccess && nrec > 0; ++h)
-            err = sp::launch_record(SP_F32, h ? b.out2 : b.out1, nullptr, a.sy, a.sz, g->nx, g->ny,
-                                    g->nz, rec->xyz, nrec,
-                                    rec->traces + (n + h - step0) * rec->trace_stride, s);
+        for (int h = 0; h < 2 && err == hipSuccess; ++h)
+            err = sp::launch_record(SP_F32, rec_args(g, rec, h ? b.out2 : b.out1, nullptr, n + h - step0), s);
         if (err != hipSuccess)
             return fail(SP_EDEVICE, "%s: launch failed at step %lld: %s", who, (long long)n,
                         hipGetErrorString(err));
@@ -498,6 +515,7 @@ int sp_wave_step_fused(const sp_grid *g, const sp_coeffs *c, double dt, double d
     }
     if (nsteps % 2) {
         sp_receivers r1;
+        const int nrec = rec ? rec->n : 0;
         if (nrec > 0) {
             r1 = *rec;
             r1.traces = rec->traces + (st->step - step0) * rec->trace_stride;
@@ -668,7 +686,6 @@ int sp_wave_step_pml(const sp_grid *g, const sp_coeffs *c, double dt, double dx,
         }
     };
     if (dec == SP_PML_TWO) split_shell();
-    const int nrec = rec ? rec->n : 0;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int64_t step0 = st->step;
     for (int k = 0; k < nsteps; ++k) {
@@ -684,6 +701,8 @@ int sp_wave_step_pml(const sp_grid *g, const sp_coeffs *c, double dt, double dx,
             b.a.out = prev + b.off;
             b.a.src.amp = amp;
         }
+        // the first launch also records the step's input (see sp_wave_step)
+        boxes[0].a.rec = rec_args(g, k > 0 ? rec : nullptr, cur, nullptr, n - 1 - step0);
         if (dec == SP_PML_TWO) {
             // inner box, then the six slabs of the shell in one launch
             err = sp::launch_sweep(boxes[0].mode, SP_F32, boxes[0].t, boxes[0].a, s);
@@ -701,9 +720,8 @@ int sp_wave_step_pml(const sp_grid *g, const sp_coeffs *c, double dt, double dx,
             for (int q = 0; q < nb && err == hipSuccess; ++q)
                 err = sp::launch_sweep(boxes[q].mode, SP_F32, boxes[q].t, boxes[q].a, s);
         }
-        if (err == hipSuccess && nrec > 0)
-            err = sp::launch_record(SP_F32, prev, nullptr, a.sy, a.sz, nx, ny, nz, rec->xyz, nrec,
-                                    rec->traces + (n - step0) * rec->trace_stride, s);
+        if (err == hipSuccess && k + 1 == nsteps)
+            err = sp::launch_record(SP_F32, rec_args(g, rec, prev, nullptr, n - step0), s);
         if (err != hipSuccess)
             return fail(SP_EDEVICE, "%s: launch failed at step %lld: %s", who, (long long)n,
                         hipGetErrorString(err));
@@ -731,17 +749,16 @@ int sp_wave_run_states(const sp_grid *g, const sp_coeffs *c, double dt, double d
                 return fail(SP_EINVAL, "sp_wave_run_states: states %d and %d overlap", j, i);
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const int nrec = rec ? rec->n : 0;
     for (int i = 0; i < nsteps; ++i) {
         a.prev = static_cast<const float *>(states[i]) + g->origin;
         a.u = static_cast<const float *>(states[i + 1]) + g->origin;
         float *out = static_cast<float *>(states[i + 2]) + g->origin;
         a.out = out;
         if (a.src.n > 0) a.src.amp = src->amp + (n0 + i) * src->amp_stride;
+        a.rec = rec_args(g, i > 0 ? rec : nullptr, a.u, nullptr, i - 1);
         hipError_t err = sp::launch_sweep(sp::MODE_WAVE, SP_F32, t, a, s);
-        if (err == hipSuccess && nrec > 0)
-            err = sp::launch_record(SP_F32, out, nullptr, a.sy, a.sz, g->nx, g->ny, g->nz,
-                                    rec->xyz, nrec, rec->traces + i * rec->trace_stride, s);
+        if (err == hipSuccess && i + 1 == nsteps)
+            err = sp::launch_record(SP_F32, rec_args(g, rec, out, nullptr, i), s);
         if (err != hipSuccess)
             return fail(SP_EDEVICE, "sp_wave_run_states: launch failed: %s", hipGetErrorString(err));
     }

@@ -49,6 +49,20 @@ struct SlabMeta {
     int nslab;
 };
 
+// Receivers of one field: traces[r] = field[x_r] (decoded with the per-slab
+// scales if `scale`), 0 outside the interior.
+struct RecArgs {
+    const void *field;       // at interior origin, storage type of the launch
+    const float *scale;      // per-slab scales of the field (FP16/BF16) or null
+    const int32_t *xyz;      // device [n][3]
+    float *traces;           // one step's row
+    int64_t sy, sz;
+    int nx, ny, nz, n;
+};
+
+// Receivers per block of a sweep's record blocks and of the record kernels.
+constexpr int REC_BLOCK = 256;
+
 // Arguments of one sweep of the streaming star kernel.  Field pointers are
 // at the interior origin and typed by the storage type of the launch.
 struct SweepArgs {
@@ -70,6 +84,8 @@ struct SweepArgs {
     float *psi;          // MODE_PML: auxiliary field on u's layout, updated in place
     float dt, alpha_dt;  // MODE_PML: time step and frequency shift times dt
     uint32_t *nonfinite; // batched MODE_WAVE: set non-zero when an output value is not finite
+    RecArgs rec;         // MODE_WAVE, MODE_PML: receivers of the input field u, recorded by
+                         // further blocks of the same launch (n = 0: none)
     int tiles_x, tiles_y, zchunk, nzc;
 };
 
@@ -91,7 +107,7 @@ int occupancy_zchunk(int64_t tiles, int nz, int per_round);
 
 // Up to MAX_BOXES boxes of one grid swept by one launch of 512-thread
 // blocks: box k takes blocks [first[k], first[k+1]), on 256x8x1 tiles if
-// wide[k], else on 32x64x1 tiles (kernel arguments: 6 x 480 B fits the
+// wide[k], else on 32x64x1 tiles (kernel arguments: 6 x 544 B fits the
 // 4 KB limit).
 constexpr int MAX_BOXES = 6;
 struct BoxSet {
@@ -105,10 +121,7 @@ hipError_t launch_sweep_boxes(int mode, const BoxSet &bs, hipStream_t s);
 bool batch_supported(const TileCfg &t);
 bool tile_supported(const TileCfg &t, int mode);
 hipError_t launch_sweep(int mode, int dtype, const TileCfg &t, const SweepArgs &a, hipStream_t s);
-// Record u at receiver points (decoding with per-slab scales if `scale`).
-hipError_t launch_record(int dtype, const void *u, const float *scale, int64_t sy, int64_t sz,
-                         int nx, int ny, int nz, const int32_t *xyz, int n, float *traces,
-                         hipStream_t s);
+hipError_t launch_record(int dtype, const RecArgs &r, hipStream_t s);
 
 // field[x_r] += scale * v[x_r]^2 * amp[r] for r < n (atomic: duplicates add).
 hipError_t launch_inject(float *field, int64_t sy, int64_t sz, const float *v, int64_t vsy,
@@ -136,18 +149,9 @@ int prep_wave(const char *who, const sp_grid *g, const sp_coeffs *c, double dt, 
 void step_args(SweepArgs &a, const sp_grid *g, void *cur, void *prev, void *out, float *meta,
                int64_t n, const float *amp, int64_t amp_stride);
 
-// Receiver recording of one grid in a batched launch (newest field).
-struct RecArgs {
-    const void *field;       // at interior origin, storage type of the launch
-    const float *scale;      // per-slab scales of the field (FP16/BF16) or null
-    const int32_t *xyz;      // device [n][3]
-    float *traces;           // this step's row
-    int64_t sy, sz;
-    int nx, ny, nz, n;
-};
-
 // Batched sweep: nblk blocks; block b computes tile table[b].y of the grid
-// whose arguments are args[table[b].x] (device arrays).
+// whose arguments are args[table[b].x] (device arrays), or, if table[b].y is
+// negative, records block -1 - table[b].y of its receivers.
 hipError_t launch_sweep_batch(int mode, int dtype, const TileCfg &t, const SweepArgs *args,
                               const int2 *table, int nblk, hipStream_t s);
 // Batched receivers: thread r records receiver rmap[r].y of grid rmap[r].x.

@@ -29,6 +29,9 @@ double now_s() {
 
 int64_t align256(int64_t b) { return (b + 255) / 256 * 256; }
 
+// Blocks that record n receivers.
+int rec_blocks(int n) { return (std::max(0, n) + sp::REC_BLOCK - 1) / sp::REC_BLOCK; }
+
 // Planes per block of a shot that shares its launch with other shots.  A
 // lone grid is split along z as far as it needs to fill the GPU (a small
 // grid into chunks shorter than this); in a batch the other shots supply
@@ -114,7 +117,8 @@ struct Group {
     int dtype;
     sp::TileCfg tile;
     std::vector<Shot *> members;     // stable pointers into the queue's shot map
-    int nblk = 0, nrec = 0;
+    int nblk = 0, nrec = 0;              // tile blocks; receivers
+    int nrb = 0;                         // record blocks (after the tile blocks)
     int64_t off_table = 0, off_rmap = 0, off_args = 0, off_recs = 0;
 };
 
@@ -165,12 +169,13 @@ int64_t shot_bytes(const sp_grid &g, const sp_grid &gv) {
 int64_t ctrl_need(const std::vector<const Shot *> &set, int k) {
     int64_t blocks = 0, recs = 0;
     for (auto *s : set) {
-        blocks += s->nblk;
+        blocks += s->nblk + rec_blocks(s->d.nrec);
         recs += s->d.nrec;
     }
     const int64_t n = (int64_t)set.size();
     return align256(blocks * 8) * 3 + align256(recs * 8) * 3 +
-           (int64_t)k * n * (align256(sizeof(sp::SweepArgs)) + align256(sizeof(sp::RecArgs))) + 4096;
+           (int64_t)k * n * (int64_t)(sizeof(sp::SweepArgs) + sizeof(sp::RecArgs)) +
+           std::min<int64_t>(n, 12) * 512 + 4096;   // at most 12 groups (storage type, tile), two aligned parts each
 }
 
 void release_shot(sp_queue *q, Shot &s) {
@@ -208,6 +213,7 @@ int rebuild(sp_queue *q, const std::vector<Shot *> &act, int k) {
         }
         gp->members.push_back(&s);
         gp->nrec += std::max(0, s.d.nrec);
+        gp->nrb += rec_blocks(s.d.nrec);
     }
     for (auto &g : q->groups) {
         for (Shot *m : g.members) {
@@ -223,7 +229,7 @@ int rebuild(sp_queue *q, const std::vector<Shot *> &act, int k) {
     int64_t off = 0;
     for (auto &g : q->groups) {
         g.off_table = off;
-        off += align256((int64_t)g.nblk * 8);
+        off += align256((int64_t)(g.nblk + g.nrb) * 8);
         g.off_rmap = off;
         off += align256((int64_t)g.nrec * 8);
     }
@@ -257,6 +263,9 @@ int rebuild(sp_queue *q, const std::vector<Shot *> &act, int k) {
             const int m = int(std::upper_bound(prefix.begin(), prefix.end(), gl) - prefix.begin()) - 1;
             table[b] = make_int2(m, gl - prefix[m]);
         }
+        int2 *rb = table + g.nblk;
+        for (size_t m = 0; m < g.members.size(); ++m)
+            for (int j = 0; j < rec_blocks(g.members[m]->d.nrec); ++j) *rb++ = make_int2((int)m, -1 - j);
         int2 *rmap = reinterpret_cast<int2 *>(q->pinned + g.off_rmap);
         int r = 0;
         for (size_t m = 0; m < g.members.size(); ++m)
@@ -270,8 +279,8 @@ int rebuild(sp_queue *q, const std::vector<Shot *> &act, int k) {
 }
 
 // The k steps of the current composition: per step and group one batched
-// sweep and one batched receiver launch, reading their arguments from the
-// control part.
+// sweep, and after the last one batched receiver launch per group, reading
+// their arguments from the control part.
 hipError_t launch_steps(sp_queue *q, int k, hipStream_t st) {
     hipError_t e = hipSuccess;
     for (int i = 0; i < k && e == hipSuccess; ++i) {
@@ -279,8 +288,10 @@ hipError_t launch_steps(sp_queue *q, int k, hipStream_t st) {
             const int nm = (int)g.members.size();
             auto *args = reinterpret_cast<const sp::SweepArgs *>(q->ctrl_dev + g.off_args) + (int64_t)i * nm;
             auto *table = reinterpret_cast<const int2 *>(q->ctrl_dev + g.off_table);
-            e = sp::launch_sweep_batch(sp::MODE_WAVE, g.dtype, g.tile, args, table, g.nblk, st);
-            if (e == hipSuccess && g.nrec > 0) {
+            // each step after the first records the step before it in the same launch
+            e = sp::launch_sweep_batch(sp::MODE_WAVE, g.dtype, g.tile, args, table,
+                                       g.nblk + (i > 0 ? g.nrb : 0), st);
+            if (e == hipSuccess && g.nrec > 0 && i + 1 == k) {
                 auto *recs = reinterpret_cast<const sp::RecArgs *>(q->ctrl_dev + g.off_recs) + (int64_t)i * nm;
                 auto *rmap = reinterpret_cast<const int2 *>(q->ctrl_dev + g.off_rmap);
                 e = sp::launch_record_batch(g.dtype, recs, rmap, g.nrec, st);
@@ -340,6 +351,7 @@ int run_chunk(sp_queue *q, int k) {
                 r.ny = s.g.ny;
                 r.nz = s.g.nz;
                 r.n = s.d.nrec;
+                if (i > 0) a.rec = recs[(int64_t)(i - 1) * nm + m];
                 std::swap(cur, prev);
             }
         }

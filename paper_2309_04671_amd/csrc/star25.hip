@@ -1041,6 +1041,19 @@ __device__ __forceinline__ void star25_body(const SweepArgs &a, const int lin) {
     }
 }
 
+// One block's receivers.
+template <typename T> __device__ __forceinline__ void record_block(const RecArgs &a, int block) {
+    const int r = block * REC_BLOCK + (int)threadIdx.x;
+    if (threadIdx.x >= REC_BLOCK || r >= a.n) return;
+    const int x = a.xyz[3 * r], y = a.xyz[3 * r + 1], z = a.xyz[3 * r + 2];
+    float val = 0.f;
+    if (x >= 0 && x < a.nx && y >= 0 && y < a.ny && z >= 0 && z < a.nz) {
+        const float sc = a.scale ? a.scale[z >> 4] : 1.f;
+        val = Io<T>::dec1(static_cast<const T *>(a.field)[(int64_t)z * a.sz + (int64_t)y * a.sy + x], sc);
+    }
+    a.traces[r] = val;
+}
+
 // Register cap of a kernel instance: the 16-bit leapfrog on its default
 // 128x16x2 tiles is held to 168 VGPRs, three waves per SIMD.  Left alone the
 // compiler takes 170-180 and drops to two waves (served batches: 342
@@ -1055,7 +1068,17 @@ template <int TX, int TY, int RY, int MODE, typename T>
 __global__ void __launch_bounds__((TX / 4) * (TY / RY))
 __attribute__((amdgpu_waves_per_eu(waves_per_simd<TX, TY, RY, MODE, T>())))
 k_star25(SweepArgs a) {
-    star25_body<TX, TY, RY, MODE, T>(a, xcd_tile(blockIdx.x, gridDim.x));
+    if constexpr (MODE == MODE_WAVE || MODE == MODE_PML) {
+        // Blocks past the tiles record the receivers of the input field, the
+        // previous step's output: a launch of its own for them after every
+        // step cost 2-5 us and the gap before it, a third of a step on the
+        // smallest grids (100x72x60, 200 receivers: 8.5 -> 6.7 us).
+        const int nblk = a.tiles_x * a.tiles_y * a.nzc;
+        if ((int)blockIdx.x >= nblk) return record_block<T>(a.rec, (int)blockIdx.x - nblk);
+        star25_body<TX, TY, RY, MODE, T>(a, xcd_tile(blockIdx.x, nblk));
+    } else {
+        star25_body<TX, TY, RY, MODE, T>(a, xcd_tile(blockIdx.x, gridDim.x));
+    }
 }
 
 // Several boxes of one grid in one launch (the absorbing layer's shell as
@@ -1078,13 +1101,15 @@ __global__ void __launch_bounds__(512) k_star25_shell(const BoxSet bs) {
 }
 
 // Batched form: block b computes tile table[b].y of grid table[b].x, whose
-// arguments are args[table[b].x].  The host lays the table out so that each
-// XCD receives contiguous tiles of the same grid.
+// arguments are args[table[b].x], or records receivers (a negative tile).  The
+// host lays the table out so that each XCD receives contiguous tiles of the
+// same grid.
 template <int TX, int TY, int RY, int MODE, typename T>
 __global__ void __launch_bounds__((TX / 4) * (TY / RY))
 __attribute__((amdgpu_waves_per_eu(waves_per_simd<TX, TY, RY, MODE, T>())))
 k_star25_batch(const SweepArgs *__restrict__ args, const int2 *__restrict__ table) {
     const int2 e = table[blockIdx.x];
+    if (e.y < 0) return record_block<T>(args[e.x].rec, -1 - e.y);
     star25_body<TX, TY, RY, MODE, T, true>(args[e.x], e.y);
 }
 
@@ -1174,19 +1199,7 @@ __global__ void __launch_bounds__(512) k_sum(const double *partial, int n, doubl
     }
 }
 
-template <typename T>
-__global__ void k_record(const T *u, const float *scale, int64_t sy, int64_t sz, int nx, int ny,
-                         int nz, const int32_t *xyz, int n, float *traces) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= n) return;
-    const int x = xyz[3 * r], y = xyz[3 * r + 1], z = xyz[3 * r + 2];
-    float val = 0.f;
-    if (x >= 0 && x < nx && y >= 0 && y < ny && z >= 0 && z < nz) {
-        const float s = scale ? scale[z >> 4] : 1.f;
-        val = Io<T>::dec1(u[(int64_t)z * sz + (int64_t)y * sy + x], s);
-    }
-    traces[r] = val;
-}
+template <typename T> __global__ void k_record(const RecArgs a) { record_block<T>(a, (int)blockIdx.x); }
 
 template <typename T>
 __global__ void k_record_batch(const RecArgs *__restrict__ recs, const int2 *__restrict__ rmap,
@@ -1238,7 +1251,8 @@ hipError_t launch_batch_cfg(int mode, const TileCfg &t, const SweepArgs *args, c
 template <int TX, int TY, int RY, typename T>
 hipError_t launch_t(int mode, const SweepArgs &a, hipStream_t s) {
     const int nblk = a.tiles_x * a.tiles_y * a.nzc;
-    const dim3 grid(nblk), block((TX / 4) * (TY / RY));
+    const dim3 grid(nblk + (a.rec.n + REC_BLOCK - 1) / REC_BLOCK), block((TX / 4) * (TY / RY));
+    static_assert((TX / 4) * (TY / RY) >= REC_BLOCK, "a record block needs REC_BLOCK threads");
     if (mode == MODE_WAVE) {
         hipLaunchKernelGGL((k_star25<TX, TY, RY, MODE_WAVE, T>), grid, block, 0, s, a);
     } else if (mode == MODE_PML) {
@@ -1294,7 +1308,7 @@ hipError_t launch_cfg(int mode, const TileCfg &t, const SweepArgs &a, hipStream_
         // the absorbing layer's x slabs: one 128-byte line per tile row
         if constexpr (std::is_same<T, float>::value) {
             if (mode == MODE_PML) {
-                const dim3 grid(a.tiles_x * a.tiles_y * a.nzc), block(256);
+                const dim3 grid(a.tiles_x * a.tiles_y * a.nzc + (a.rec.n + REC_BLOCK - 1) / REC_BLOCK), block(256);
                 hipLaunchKernelGGL((k_star25<32, 32, 1, MODE_PML, float>), grid, block, 0, s, a);
                 return hipGetLastError();
             }
@@ -1473,25 +1487,13 @@ hipError_t launch_sum(const double *partial, int n, double *out, hipStream_t s) 
     return hipGetLastError();
 }
 
-hipError_t launch_record(int dtype, const void *u, const float *scale, int64_t sy, int64_t sz,
-                         int nx, int ny, int nz, const int32_t *xyz, int n, float *traces,
-                         hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    const int bs = 256;
-    const dim3 g((n + bs - 1) / bs), b(bs);
+hipError_t launch_record(int dtype, const RecArgs &r, hipStream_t s) {
+    if (r.n <= 0) return hipSuccess;
+    const dim3 g((r.n + REC_BLOCK - 1) / REC_BLOCK), b(REC_BLOCK);
     switch (dtype) {
-        case SP_F32:
-            hipLaunchKernelGGL(k_record<float>, g, b, 0, s, static_cast<const float *>(u), scale,
-                               sy, sz, nx, ny, nz, xyz, n, traces);
-            break;
-        case SP_F16:
-            hipLaunchKernelGGL(k_record<_Float16>, g, b, 0, s, static_cast<const _Float16 *>(u),
-                               scale, sy, sz, nx, ny, nz, xyz, n, traces);
-            break;
-        case SP_BF16:
-            hipLaunchKernelGGL(k_record<__bf16>, g, b, 0, s, static_cast<const __bf16 *>(u),
-                               scale, sy, sz, nx, ny, nz, xyz, n, traces);
-            break;
+        case SP_F32: hipLaunchKernelGGL(k_record<float>, g, b, 0, s, r); break;
+        case SP_F16: hipLaunchKernelGGL(k_record<_Float16>, g, b, 0, s, r); break;
+        case SP_BF16: hipLaunchKernelGGL(k_record<__bf16>, g, b, 0, s, r); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
