@@ -110,7 +110,7 @@ void fill_tiling(sp::SweepArgs &a, const sp::TileCfg &t) {
 // Launch configuration for a grid; SP_TILE=TXxTYxRY[xZC] overrides it for
 // tuning.  Returns false (with the error set) for a configuration that is
 // not compiled in.
-bool tiles_for(const sp_grid *g, sp::TileCfg *out, const char *who, int mode = sp::MODE_WAVE) {
+bool tiles_for(const sp_grid *g, sp::TileCfg *out, const char *who, int mode) {
     sp::TileCfg t = sp::choose_tiles(g->nx, g->ny, g->nz, g->dtype, mode);
     // Optional override for tuning: SP_TILE=TXxTYxRY[xZC]
     if (const char *e = std::getenv("SP_TILE")) {
@@ -287,7 +287,7 @@ namespace sp {
 // Validation and argument setup shared by the leapfrog entry points.
 int prep_wave(const char *who, const sp_grid *g, const sp_coeffs *c, double dt, double dx,
               const sp_grid *gv, const float *v, const sp_sources *src, const sp_receivers *rec,
-              sp::SweepArgs *a, sp::TileCfg *t) {
+              sp::SweepArgs *a, sp::TileCfg *t, int mode) {
     if (int e = check_grid(g, who)) return e;
     if (int e = check_grid(gv, who)) return e;
     if (gv->dtype != SP_F32 || gv->nx != g->nx || gv->ny != g->ny || gv->nz != g->nz)
@@ -319,7 +319,7 @@ int prep_wave(const char *who, const sp_grid *g, const sp_coeffs *c, double dt, 
         if (rec->n > 0 && rec->trace_stride < rec->n)
             return fail(SP_EINVAL, "%s: trace_stride < n", who);
     }
-    if (!tiles_for(g, t, who)) return SP_EINVAL;
+    if (!tiles_for(g, t, who, mode)) return SP_EINVAL;
     std::memset(a, 0, sizeof *a);
     a->nx = g->nx;
     a->ny = g->ny;
@@ -896,7 +896,7 @@ namespace {
 int energy_prep(const char *who, const sp_grid *g, const sp_coeffs *c, double dt, double dx,
                 const sp_grid *gv, const float *v, const void *u0, const void *u1, double *out,
                 sp::SweepArgs *a, sp::TileCfg *t, int *nblk) {
-    if (int e = prep_wave(who, g, c, dt, dx, gv, v, nullptr, nullptr, a, t)) return e;
+    if (int e = prep_wave(who, g, c, dt, dx, gv, v, nullptr, nullptr, a, t, sp::MODE_ENERGY)) return e;
     if (g->dtype != SP_F32) return fail(SP_EUNSUPPORTED, "%s: FP32 grids only", who);
     if (!u0 || !u1 || !out) return fail(SP_EINVAL, "%s: NULL argument", who);
     if (!aligned16(u0) || !aligned16(u1) || (reinterpret_cast<uintptr_t>(out) & 7u))

@@ -141,10 +141,11 @@ hipError_t launch_sum(const double *partial, int n, double *out, hipStream_t s);
 // Error reporting shared by the C-ABI translation units (thread-local message).
 int fail(int code, const char *fmt, ...);
 int ok();
-// Validate the arguments common to the leapfrog calls and fill a, t.
+// Validate the arguments common to the leapfrog calls and fill a, t (the
+// configuration of a sweep of that mode).
 int prep_wave(const char *who, const sp_grid *g, const sp_coeffs *c, double dt, double dx,
               const sp_grid *gv, const float *v, const sp_sources *src, const sp_receivers *rec,
-              SweepArgs *a, TileCfg *t);
+              SweepArgs *a, TileCfg *t, int mode = MODE_WAVE);
 // Per-step pointers (fields given by allocation base), slab records and source row.
 void step_args(SweepArgs &a, const sp_grid *g, void *cur, void *prev, void *out, float *meta,
                int64_t n, const float *amp, int64_t amp_stride);

@@ -30,6 +30,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <cmath>
 #include <type_traits>
 
@@ -1377,8 +1378,7 @@ int occupancy_zchunk(int64_t tiles, int nz, int per_round) {
     // per_round blocks times zc / (zc + 8) (each chunk also streams 8
     // planes of start-up).  This keeps one chunk per tile when the tiles
     // fill whole rounds (1024^2 planes: 256 tiles) and avoids, for example,
-    // 288 blocks on a 768^2 plane (1.125 rounds: 64-plane chunks run 30 %
-    // faster there, measured).
+    // 288 blocks on a 768^2 plane (1.125 rounds).
     //
     // A grid too small to fill one round even with 16-plane chunks is
     // latency-bound: all its blocks run at once, each for its chunk plus the
@@ -1406,48 +1406,126 @@ int occupancy_zchunk(int64_t tiles, int nz, int per_round) {
     return (nz + best_k - 1) / best_k;
 }
 
+// Leapfrog and apply sweeps: tile and z-split by the time a launch is
+// expected to take, over the candidates below and the splits of z into at
+// most 12 chunks or into chunks of at most 32 planes:
+//     (us per plane of the blocks that share a CU, at least the plane's
+//      latency) x (planes per block + start-up) + a cost per block.
+// A tile that has a CU to itself runs in whole rounds of 256 blocks; several
+// small blocks share a CU and fill one another's tails.  The rates are fitted
+// to sweeps of every tile and split over 15 grids from 64^3 to 512^3 on live
+// data, for grids whose fields fit the L2 caches (32 MB) and larger ones.
+// What they come to:
+//  * 256x16 and 128x32 tiles read the least halo but waste what a tile has
+//    past a ragged edge and the CUs past a whole round: 200^3 runs 29.5 us
+//    on 256x16 tiles of 12 planes, 37.6 on three narrow tiles per row;
+//  * 64x16 tiles cost half as much again per point, three (FP32) or four
+//    (16 bits) to a CU, and fit any extent: 300x280x200 56 us against 64,
+//    128x120x96 7.5 against 9.1, FP16 at 300x280x200 45 against 56;
+//  * small grids are latency-bound and want every CU busy with short blocks
+//    (16-bit grids had kept chunks of at least 16 planes: 64^3 18.5 us per
+//    step, 7.6 with 2-plane chunks); a 16-bit block also costs its slab
+//    records (an atomic at the end, dependent loads at the start).
+namespace {
+
+struct SweepRate {
+    int tx, ty, ry;
+    int occ;                 // blocks that share a CU
+    // CU time of one plane of a block and least time of a plane, with the
+    // fields in the L2 caches, in the 256 MB behind them, and in HBM
+    struct {
+        double us, lat;
+    } at[3];
+};
+
+// bytes: per point, of all fields the sweep touches; alone: planes of start-up
+// of a block that has its CU to itself, cached; block_us: time of 256 further
+// blocks.
+TileCfg fastest_sweep(const SweepRate *r, int n, int nx, int ny, int nz, int bytes, double alone, double block_us) {
+    const double total = (double)nx * ny * nz * bytes;
+    const int where = total < 36e6 ? 0 : total < 240e6 ? 1 : 2;
+    TileCfg best = {};
+    double least = -1.0;
+    for (int i = 0; i < n; ++i) {
+        const int64_t tiles = (int64_t)((nx + r[i].tx - 1) / r[i].tx) * ((ny + r[i].ty - 1) / r[i].ty);
+        const int occ = r[i].occ;
+        const double us = r[i].at[where].us, lat = r[i].at[where].lat;
+        // The planes streamed ahead of a chunk cost hardly more than a
+        // latency, which other blocks on the CU hide; for a block alone on
+        // its CU their memory traffic too (half of an apply sweep's is u).
+        const double start = occ > 1 || where == 0 ? 0.7 : where == 2 ? std::max(alone, 2.0) : alone;
+        // integer rounding throughout: this runs in every call, and with
+        // floating-point ceilings it was a microsecond of a 10 us call
+        const int64_t slots = 256 * occ;
+        auto consider = [&](int chunks) {
+            const int zc = (int)((unsigned)(nz + chunks - 1) / (unsigned)chunks);
+            const int64_t nblk = tiles * chunks;
+            int64_t units = (nblk + 255) & ~(int64_t)255;     // 256 blocks per CU-filling round
+            if (occ > 1 && nblk > slots) {
+                // several blocks per CU: the last round is shared out, and
+                // costs about a third of the slots it leaves empty
+                const int64_t full = nblk < ((int64_t)1 << 31)
+                                         ? (int64_t)((unsigned)(nblk + slots - 1) / (unsigned)slots) * slots
+                                         : (nblk + slots - 1) / slots * slots;
+                units = nblk + (full - nblk) * 45 / 128;
+            }
+            const double t = std::max((double)units * us * (1.0 / 256), lat) * (zc + start) +
+                             block_us * (1.0 / 256) * (double)nblk;
+            if (least < 0 || t < least) {
+                least = t;
+                best.tx = r[i].tx;
+                best.ty = r[i].ty;
+                best.ry = r[i].ry;
+                best.zchunk = zc;
+            }
+        };
+        for (int k = 1; k <= 12 && k <= nz; ++k) consider(k);
+        for (int zc = std::min(32, (nz - 1) / 12); zc >= 1; zc -= zc > 12 ? 2 : 1)
+            consider((int)((unsigned)(nz + zc - 1) / (unsigned)zc));
+    }
+    return best;
+}
+
+}  // namespace
+
 TileCfg choose_tiles(int nx, int ny, int nz, int dtype, int mode) {
-    // Widest tile that does not waste more than a quarter of its columns on
-    // the ragged x edge: wide tiles keep the x-halo (one 128-byte line per
-    // side per row) and the y-halo rows small relative to the tile, and two
-    // rows per thread share their y-neighbour reads.  The candidates depend
-    // on the storage type, because what limits each kernel differs:
-    //  * FP32 (231 VGPRs, 16-byte accesses): 512-thread 256x16x2 tiles, one
-    //    block per CU, z split only when there are fewer than 256 tiles
-    //    (the leapfrog on grids that need 16-plane chunks: 256x16x1);
-    //  * FP16 and BF16 (the raw 16-bit body, held to 168 VGPRs for three
-    //    waves per SIMD, 8-byte accesses): 256-thread 128x16x2 tiles and many
-    //    short z-chunks (about 4096 blocks) so that the CUs stay evenly
-    //    loaded (BF16 at 512^3: 453 GPts/s against 345 on the 1024-thread
-    //    256x16x1 tiles the decoding body had used);
-    //  * the FP32 APPLY sweep (8 B per point) runs best on 128x32x2 tiles
-    //    with about 256 blocks (one long z-chunk per tile at 1024^2),
-    //    measured on live data: constant or overflowed fields run the same
-    //    kernel faster and had favoured other tiles;
-    //  * the absorbing-layer mode runs one row per thread in 512-thread
-    //    256x8x1 tiles, 64x16x1 or 32x32x1 for narrow boxes (the x slabs),
-    //    with the FP32 rule for the z-split;
-    //  * the fused adjoint sweep (two stencil fields per thread) runs one
-    //    row per thread in 512-thread 128x16x1 tiles, 64x16x1 for narrow
-    //    grids, with the FP32 rule for the z-split (256^3 x 1000 forward
-    //    plus backward: 0.220 s against 0.224 on 256x8x1 and 0.233 on
-    //    64x16x1 tiles);
-    // z-chunks are at least 16 planes (each chunk re-reads 8 planes of u,
-    // mostly from L2) unless the grid is too small to fill the GPU (see
-    // occupancy_zchunk).  These targets are measured optima on MI355X.
+    static const SweepRate r32[3] = {{256, 16, 2, 1, {{1.30, 1.30}, {1.95, 1.95}, {2.75, 2.75}}},
+                                     {128, 16, 2, 2, {{0.90, 1.27}, {1.24, 2.00}, {1.52, 2.20}}},
+                                     {64, 16, 1, 3, {{0.47, 0.70}, {0.70, 1.30}, {0.82, 1.60}}}};
+    static const SweepRate rap[3] = {{128, 32, 2, 1, {{1.10, 1.10}, {1.25, 1.25}, {1.45, 1.45}}},
+                                     {256, 16, 2, 1, {{1.20, 1.20}, {1.28, 1.28}, {1.53, 1.53}}},
+                                     {64, 16, 1, 4, {{0.27, 0.42}, {0.49, 0.80}, {0.46, 0.90}}}};
+    static const SweepRate r16[2] = {{128, 16, 2, 3, {{0.60, 1.00}, {0.88, 2.00}, {0.90, 2.40}}},
+                                     {64, 16, 1, 4, {{0.30, 0.50}, {0.42, 1.45}, {0.48, 2.00}}}};
+    if (mode == MODE_WAVE || mode == MODE_APPLY) {
+        TileCfg t = dtype != SP_F32       ? fastest_sweep(r16, 2, nx, ny, nz, 10, 0.7, 1.0)
+                    : mode == MODE_APPLY ? fastest_sweep(rap, 3, nx, ny, nz, 8, 4.0, 0.0)
+                                         : fastest_sweep(r32, 3, nx, ny, nz, 16, 0.7, 0.0);
+        // Short chunks of the FP32 leapfrog hide more latency with four
+        // waves per SIMD (1024-thread blocks, one row per thread) than with
+        // two: 256^3 360 against 347 GPts/s, 512x300x256 107 against 110 us,
+        // 500x420x390 252 against 257; 1024x1024x512 350 against 355 GPts/s.
+        if (dtype == SP_F32 && mode == MODE_WAVE && t.tx == 256 && t.zchunk <= 48) t.ry = 1;
+        return t;
+    }
+    // The other sweeps take the widest tile that does not waste more than a
+    // quarter of its columns on the ragged x edge, and the z-split whose
+    // blocks (`want` of them at a time: one 512-thread or two 256-thread
+    // blocks per CU) fill the GPU best:
+    //  * gradient and energy: 512-thread 256x16x2 tiles, one block per CU;
+    //  * the absorbing-layer mode: one row per thread in 512-thread 256x8x1
+    //    tiles, 64x16x1 or 32x32x1 for narrow boxes (the x slabs);
+    //  * the fused adjoint sweep (two stencil fields per thread): one row per
+    //    thread in 512-thread 128x16x1 tiles, 64x16x1 for narrow grids (256^3
+    //    x 1000 forward plus backward: 0.220 s against 0.224 on 256x8x1 and
+    //    0.233 on 64x16x1 tiles).
     struct Cand {
-        int tx, ty, ry, want, min_tiles_x;
+        int tx, ty, ry, want;
     };
-    static const Cand c32[3] = {{256, 16, 2, 256, 1}, {128, 16, 2, 512, 1}, {64, 16, 1, 512, 1}};
-    static const Cand c16[3] = {{128, 16, 2, 4096, 1}, {128, 16, 2, 4096, 1}, {64, 16, 1, 4096, 1}};
-    static const Cand cap[3] = {{128, 32, 2, 256, 1}, {128, 16, 2, 512, 1}, {64, 16, 1, 512, 1}};
-    static const Cand cpm[3] = {{256, 8, 1, 256, 1}, {64, 16, 1, 512, 1}, {32, 32, 1, 512, 1}};
-    static const Cand cad[3] = {{128, 16, 1, 256, 1}, {64, 16, 1, 512, 1}, {64, 16, 1, 512, 1}};
-    const Cand *cand = dtype != SP_F32       ? c16
-                       : mode == MODE_APPLY ? cap
-                       : mode == MODE_PML   ? cpm
-                       : mode == MODE_ADJ   ? cad
-                                            : c32;
+    static const Cand c32[3] = {{256, 16, 2, 256}, {128, 16, 2, 512}, {64, 16, 1, 512}};
+    static const Cand cpm[3] = {{256, 8, 1, 256}, {64, 16, 1, 512}, {32, 32, 1, 512}};
+    static const Cand cad[3] = {{128, 16, 1, 256}, {64, 16, 1, 512}, {64, 16, 1, 512}};
+    const Cand *cand = mode == MODE_PML ? cpm : mode == MODE_ADJ ? cad : c32;
     TileCfg t;
     int want = 256;
     for (int c = 0; c < 3; ++c) {
@@ -1456,26 +1534,10 @@ TileCfg choose_tiles(int nx, int ny, int nz, int dtype, int mode) {
         t.ry = cand[c].ry;
         want = cand[c].want;
         const int tiles_x = (nx + t.tx - 1) / t.tx;
-        if ((4 * tiles_x * t.tx <= 5 * nx && tiles_x >= cand[c].min_tiles_x) || c == 2) break;
+        if (4 * tiles_x * t.tx <= 5 * nx || c == 2) break;
     }
     const int tiles = ((nx + t.tx - 1) / t.tx) * ((ny + t.ty - 1) / t.ty);
-    int zc;
-    if (cand == c32 || cand == cpm || cand == cap || cand == cad) {
-        // FP32 sweeps (leapfrog, gradient, energy, layer, apply): `want`
-        // blocks fill the GPU once (one 512-thread or two 256-thread blocks
-        // per CU).
-        zc = occupancy_zchunk(tiles, nz, want);
-        // A leapfrog grid this small fills the GPU only with the shortest
-        // chunks; there four waves per SIMD (1024-thread 256x16x1 tiles,
-        // one row per thread, same tile count) hide more latency than the
-        // two of 256x16x2 (256^3: 360 against 347 GPts/s, measured).
-        if (cand == c32 && mode == MODE_WAVE && t.tx == 256 && t.ry == 2 && zc <= 16 && nz > 16)
-            t.ry = 1;
-    } else {
-        const int chunks = (want + tiles - 1) / tiles;
-        zc = (nz + chunks - 1) / chunks;
-        if (zc < 16) zc = 16;
-    }
+    int zc = occupancy_zchunk(tiles, nz, want);
     if (zc > nz) zc = nz;
     t.zchunk = zc < 1 ? 1 : zc;
     return t;
