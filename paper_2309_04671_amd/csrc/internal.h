@@ -100,6 +100,25 @@ struct TileCfg {
     int zchunk;          // planes per block
 };
 
+// What a tile of a streaming sweep costs (see fastest_sweep).
+struct SweepRate {
+    int tx, ty, ry;
+    int occ;                 // blocks that share a CU
+    // CU time of one plane of a block and least time of a plane (us), with
+    // the fields in the L2 caches, in the 256 MB behind them, and in HBM
+    struct {
+        double us, lat;
+    } at[3];
+};
+// Planes that a block streams before its first output, in planes of its time:
+// one that shares its CU, and one alone on it with the fields cached / in HBM.
+struct SweepStart {
+    double shared, alone, alone_hbm;
+};
+// Tile and z-split of a sweep by expected launch time.  bytes: per point, of
+// all fields the sweep touches; block_us: time of 256 further blocks.
+TileCfg fastest_sweep(const SweepRate *r, int n, int nx, int ny, int nz, int bytes, SweepStart start,
+                      double block_us);
 // Launch configuration of the k_star25 sweeps for a grid, storage type and mode.
 TileCfg choose_tiles(int nx, int ny, int nz, int dtype, int mode);
 // Planes per block for `tiles` xy tiles when per_round blocks fill the GPU.
@@ -199,8 +218,10 @@ struct SuiteArgs {
 // axes.  shape 0 = star, 1 = box.
 hipError_t launch_suite(int shape, int ndim, int radius, const float *w, const SuiteArgs &a,
                         hipStream_t s);
-// The 3D box of radius 2..4, w as above, on the FP32 matrix cores.
+// The 3D box of radius 2..4 and, on large planes, the 2D box of radius 4, w as
+// above, on the FP32 matrix cores.
 hipError_t launch_box3(int radius, const float *w, const SuiteArgs &a, hipStream_t s);
+hipError_t launch_box2r4(const float *w, const SuiteArgs &a, hipStream_t s);
 
 // eta = eta_max * sum over axes (d_a / width)^2 on every cell of the padded
 // extent, d_a = max(0, width - 1 - a, a - (n_a - width)).

@@ -1426,22 +1426,8 @@ int occupancy_zchunk(int64_t tiles, int nz, int per_round) {
 //    (16-bit grids had kept chunks of at least 16 planes: 64^3 18.5 us per
 //    step, 7.6 with 2-plane chunks); a 16-bit block also costs its slab
 //    records (an atomic at the end, dependent loads at the start).
-namespace {
-
-struct SweepRate {
-    int tx, ty, ry;
-    int occ;                 // blocks that share a CU
-    // CU time of one plane of a block and least time of a plane, with the
-    // fields in the L2 caches, in the 256 MB behind them, and in HBM
-    struct {
-        double us, lat;
-    } at[3];
-};
-
-// bytes: per point, of all fields the sweep touches; alone: planes of start-up
-// of a block that has its CU to itself, cached; block_us: time of 256 further
-// blocks.
-TileCfg fastest_sweep(const SweepRate *r, int n, int nx, int ny, int nz, int bytes, double alone, double block_us) {
+TileCfg fastest_sweep(const SweepRate *r, int n, int nx, int ny, int nz, int bytes, SweepStart start_up,
+                      double block_us) {
     const double total = (double)nx * ny * nz * bytes;
     const int where = total < 36e6 ? 0 : total < 240e6 ? 1 : 2;
     TileCfg best = {};
@@ -1450,10 +1436,7 @@ TileCfg fastest_sweep(const SweepRate *r, int n, int nx, int ny, int nz, int byt
         const int64_t tiles = (int64_t)((nx + r[i].tx - 1) / r[i].tx) * ((ny + r[i].ty - 1) / r[i].ty);
         const int occ = r[i].occ;
         const double us = r[i].at[where].us, lat = r[i].at[where].lat;
-        // The planes streamed ahead of a chunk cost hardly more than a
-        // latency, which other blocks on the CU hide; for a block alone on
-        // its CU their memory traffic too (half of an apply sweep's is u).
-        const double start = occ > 1 || where == 0 ? 0.7 : where == 2 ? std::max(alone, 2.0) : alone;
+        const double start = occ > 1 ? start_up.shared : where == 2 ? start_up.alone_hbm : start_up.alone;
         // integer rounding throughout: this runs in every call, and with
         // floating-point ceilings it was a microsecond of a 10 us call
         const int64_t slots = 256 * occ;
@@ -1486,8 +1469,6 @@ TileCfg fastest_sweep(const SweepRate *r, int n, int nx, int ny, int nz, int byt
     return best;
 }
 
-}  // namespace
-
 TileCfg choose_tiles(int nx, int ny, int nz, int dtype, int mode) {
     static const SweepRate r32[3] = {{256, 16, 2, 1, {{1.30, 1.30}, {1.95, 1.95}, {2.75, 2.75}}},
                                      {128, 16, 2, 2, {{0.90, 1.27}, {1.24, 2.00}, {1.52, 2.20}}},
@@ -1498,9 +1479,12 @@ TileCfg choose_tiles(int nx, int ny, int nz, int dtype, int mode) {
     static const SweepRate r16[2] = {{128, 16, 2, 3, {{0.60, 1.00}, {0.88, 2.00}, {0.90, 2.40}}},
                                      {64, 16, 1, 4, {{0.30, 0.50}, {0.42, 1.45}, {0.48, 2.00}}}};
     if (mode == MODE_WAVE || mode == MODE_APPLY) {
-        TileCfg t = dtype != SP_F32       ? fastest_sweep(r16, 2, nx, ny, nz, 10, 0.7, 1.0)
-                    : mode == MODE_APPLY ? fastest_sweep(rap, 3, nx, ny, nz, 8, 4.0, 0.0)
-                                         : fastest_sweep(r32, 3, nx, ny, nz, 16, 0.7, 0.0);
+        // The planes streamed ahead of a chunk cost hardly more than a
+        // latency, which other blocks on the CU hide; for a block alone on
+        // its CU their memory traffic too (half of an apply sweep's is u).
+        TileCfg t = dtype != SP_F32       ? fastest_sweep(r16, 2, nx, ny, nz, 10, {0.7, 0.7, 2.0}, 1.0)
+                    : mode == MODE_APPLY ? fastest_sweep(rap, 3, nx, ny, nz, 8, {0.7, 4.0, 4.0}, 0.0)
+                                         : fastest_sweep(r32, 3, nx, ny, nz, 16, {0.7, 0.7, 2.0}, 0.0);
         // Short chunks of the FP32 leapfrog hide more latency with four
         // waves per SIMD (1024-thread blocks, one row per thread) than with
         // two: 256^3 360 against 347 GPts/s, 512x300x256 107 against 110 us,

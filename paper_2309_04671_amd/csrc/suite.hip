@@ -7,14 +7,17 @@
 // 2D (one wave = one 256-point-wide strip of a plane, streaming along y):
 //  * a lane owns 4 consecutive x points; rows y-r .. y+r of its 4 columns
 //    sit in a register queue, each row fetched from HBM once per strip;
-//  * x-neighbours come from the two adjacent 16-byte chunks of the row (L1/L2
-//    hits: the neighbouring lanes fetched them), for every queued row of a
-//    box and for the centre row of a star;
+//  * x-neighbours: a box loads the two adjacent 16-byte chunks of every queued
+//    row (L1/L2 hits: the neighbouring lanes fetched them); a star needs them
+//    for its centre row only and takes them from the neighbouring lanes'
+//    registers, the strip's two edge chunks from one load of two lines (8192^2,
+//    us per sweep with the two chunks loaded -> now: r = 1 107 -> 98, r = 4
+//    119 -> 108);
 //  * no LDS and no barriers: the four waves of a block are independent, and
 //    loads of row y+r+1 are in flight while row y is computed.
 // 3D stars and the box of radius 1 (larger boxes: box.hip): a workgroup = a
-// 256 x TY tile streaming along z (the accumulating, or
-// semi-stencil, arrangement);
+// TX x TY tile streaming along z (the accumulating, or semi-stencil,
+// arrangement);
 //  * each plane of the tile plus an r-row, 4-column frame (corners included)
 //    is fetched once into a double-buffered LDS slot, one barrier per plane;
 //  * the plane's contribution to the 2r+1 output planes it touches is added
@@ -27,8 +30,11 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "internal.h"
 #include "kcommon.h"
+#include "log.h"
 
 namespace sp {
 
@@ -57,6 +63,14 @@ struct Tile2 {
     int tiles_x, ychunk, groups;   // groups: blocks per strip and plane
 };
 
+// v of the lane before / after this one; lane 0 / 63 keeps `edge`.
+__device__ __forceinline__ float from_left(float edge, float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(edge), __float_as_int(v), 0x138, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float from_right(float edge, float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(edge), __float_as_int(v), 0x130, 0xf, 0xf, false));
+}
+
 template <int R, bool BOX>
 __global__ __launch_bounds__(64 * WAVES2) void k_suite2(SuiteArgs a, Tile2 t,
                                                         Wts<WCount<R, BOX, 2>::value> W) {
@@ -71,14 +85,18 @@ __global__ __launch_bounds__(64 * WAVES2) void k_suite2(SuiteArgs a, Tile2 t,
     const int yb = (grp * WAVES2 + wv) * t.ychunk;
     if (yb >= a.ny) return;                              // whole wave
     const int ye = min(yb + t.ychunk, a.ny);
-    const int x = tx * 256 + lane * 4;
-    // lanes past the row end load a valid chunk and store nothing
-    const int xl = min(x, (a.nx - 1) & ~3);
+    const int x0 = tx * 256, x = x0 + lane * 4;
+    // lanes past the row end load a valid chunk and store nothing (star: the
+    // first of them the frame chunk its left neighbour reads)
+    const int xf = (a.nx + 3) & ~3;
+    const int xl = min(x, BOX ? (a.nx - 1) & ~3 : xf);
     const float *src = a.u + (int64_t)z * a.sz + xl;
+    // star: the chunk before the strip (lanes 0..31) or after it
+    const float *edge = a.u + (int64_t)z * a.sz + (lane < 32 ? x0 - 4 : min(x0 + 256, xf));
     float *dst = a.out + (int64_t)z * a.sz + x;
     const int nst = a.nx - x;                           // values this lane stores per row
 
-    f4v qc[D], ql[QS], qr[QS];
+    f4v qc[D], ql[QS], qr[QS], e;
     for (int k = 0; k < D; ++k) {
         const float *p = src + (int64_t)(yb - R + k) * a.sy;
         qc[k] = ld4(p);
@@ -87,25 +105,24 @@ __global__ __launch_bounds__(64 * WAVES2) void k_suite2(SuiteArgs a, Tile2 t,
             qr[k] = ld4(p + 4);
         }
     }
-    if constexpr (!BOX) {
-        const float *p = src + (int64_t)yb * a.sy;
-        ql[0] = ld4(p - 4);
-        qr[0] = ld4(p + 4);
-    }
+    if constexpr (!BOX) e = ld4(edge + (int64_t)yb * a.sy);
 
     for (int y = yb; y < ye; ++y) {
         // fetch ahead: row y+r+1 (clamped: the last pass re-reads a row)
         const int yn = min(y + R + 1, ye + R - 1);
         const float *pn = src + (int64_t)yn * a.sy;
         const f4v nc = ld4(pn);
-        f4v nl, nr;
+        f4v nl, nr, ne;
         if constexpr (BOX) {
             nl = ld4(pn - 4);
             nr = ld4(pn + 4);
         } else {
-            const float *pc = src + (int64_t)min(y + 1, ye - 1) * a.sy;
-            nl = ld4(pc - 4);
-            nr = ld4(pc + 4);
+            ne = ld4(edge + (int64_t)min(y + 1, ye - 1) * a.sy);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                ql[0][i] = i >= 4 - R ? from_left(e[i], qc[R][i]) : 0.f;
+                qr[0][i] = i < R ? from_right(e[i], qc[R][i]) : 0.f;
+            }
         }
 
         f4v res;
@@ -142,8 +159,7 @@ __global__ __launch_bounds__(64 * WAVES2) void k_suite2(SuiteArgs a, Tile2 t,
             ql[D - 1] = nl;
             qr[D - 1] = nr;
         } else {
-            ql[0] = nl;
-            qr[0] = nr;
+            e = ne;
         }
     }
 }
@@ -152,24 +168,22 @@ struct Tile3 {
     int tiles_x, tiles_y, zchunk;
 };
 
-constexpr int LC = 66;         // 16-byte chunks per LDS row: x0-4 .. x0+259
-
-template <int R, bool BOX, int TY, int RY>
-__global__ __launch_bounds__(64 * TY / RY) void k_suite3(SuiteArgs a, Tile3 t,
-                                                        Wts<WCount<R, BOX, 3>::value> W) {
-    constexpr int NT = 64 * TY / RY, D = 2 * R + 1;
+template <int R, bool BOX, int TX, int NT, int RY>
+__global__ __launch_bounds__(NT) void k_suite3(SuiteArgs a, Tile3 t, Wts<WCount<R, BOX, 3>::value> W) {
+    constexpr int LX = TX / 4, TY = RY * NT / LX, D = 2 * R + 1;
+    constexpr int LC = LX + 2;                   // 16-byte chunks per LDS row: x0-4 .. x0+TX+3
     constexpr int LR = TY + 2 * R;               // LDS rows: tile plus r-row frame
     constexpr int NCH = LR * LC;
     constexpr int K = (NCH + NT - 1) / NT;       // chunks fetched per thread and plane
     __shared__ f4v lds[2][NCH];
 
-    const int tid = threadIdx.x, lane = tid & 63, rg = tid >> 6;
+    const int tid = threadIdx.x, lane = tid % LX, rg = tid / LX;
     int lin = xcd_tile(blockIdx.x, gridDim.x);
     const int tx = lin % t.tiles_x;
     lin /= t.tiles_x;
     const int ty = lin % t.tiles_y;
     const int zc = lin / t.tiles_y;
-    const int x0 = tx * 256, y0 = ty * TY;
+    const int x0 = tx * TX, y0 = ty * TY;
     const int zb = zc * t.zchunk, ze = min(zb + t.zchunk, a.nz);
 
     // This thread's chunks of every plane: in-plane element offsets (0 for a
@@ -298,11 +312,25 @@ template <int R, bool BOX>
 hipError_t run2(const float *w, const SuiteArgs &a, hipStream_t s) {
     Tile2 t;
     t.tiles_x = (a.nx + 255) / 256;
-    // rows per wave: about 4096 waves (16 per CU; measured best), at least
-    // 8r rows so the 2r re-read rows stay a small share
-    const int64_t strips = (int64_t)t.tiles_x * a.nz;
-    int64_t yc = (strips * a.ny + 4095) / 4096;
-    yc = std::max<int64_t>(yc, 8 * R);
+    // Rows per wave: few.  A short chunk loads all its rows at once instead
+    // of waiting for one after another, and its 2r re-read rows come from the
+    // caches that the neighbouring chunks (next blocks on the XCD) fetch them
+    // into; fewer still where a plane would leave under 2048 waves.  Boxes
+    // load three chunks per re-read row: those of radius 1 and 2, and radius 3
+    // where the plane comes from HBM, keep chunks as long as 4096 waves allow.
+    // Measured over 2 to 64 rows; us per sweep, at least 8r rows and 4096
+    // waves before -> now: star r = 4 5000x4100 31.1 -> 30.2, 2174x2965 16.8
+    // -> 11.5, 400x350 11.5 -> 2.8; box r = 3 5000x4100 48 -> 45, 2174x2965
+    // 26.6 -> 18.0, 1200x900 18.9 -> 6.6.
+    const int64_t strips = (int64_t)t.tiles_x * a.nz, rows = strips * a.ny;
+    const bool hbm = (double)a.nx * a.ny * a.nz * 8 > 240e6;
+    int most = BOX ? 6 : (hbm ? 6 : 4);
+    int64_t waves = 2048;
+    if (BOX && (hbm || R < 3)) {
+        most = R == 3 ? 32 : 64;
+        waves = 4096;
+    }
+    const int64_t yc = std::min<int64_t>(most, (rows + waves - 1) / waves);
     t.ychunk = (int)std::min<int64_t>(yc, a.ny);
     const int nchunks = (a.ny + t.ychunk - 1) / t.ychunk;
     t.groups = (nchunks + WAVES2 - 1) / WAVES2;
@@ -314,32 +342,69 @@ hipError_t run2(const float *w, const SuiteArgs &a, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <int R, bool BOX>
-hipError_t run3(const float *w, const SuiteArgs &a, hipStream_t s) {
-    constexpr int TY = 16, RY = 2;
+template <int R, bool BOX, int TX, int NT, int RY>
+hipError_t run3t(const TileCfg &c, const float *w, const SuiteArgs &a, hipStream_t s) {
     Tile3 t;
-    t.tiles_x = (a.nx + 255) / 256;
-    t.tiles_y = (a.ny + TY - 1) / TY;
-    const int64_t tiles = (int64_t)t.tiles_x * t.tiles_y;
-    // split z only as far as needed for about one block per CU: longer
-    // chunks re-read fewer frame planes (measured best)
-    const int64_t want = 256;
-    int64_t chunks = (want + tiles - 1) / tiles;
-    int64_t zc = (a.nz + chunks - 1) / chunks;
-    zc = std::max<int64_t>(zc, std::min<int64_t>(4 * R, a.nz));
-    t.zchunk = (int)std::min<int64_t>(zc, a.nz);
-    const int64_t nblk = tiles * ((a.nz + t.zchunk - 1) / t.zchunk);
+    t.tiles_x = (a.nx + c.tx - 1) / c.tx;
+    t.tiles_y = (a.ny + c.ty - 1) / c.ty;
+    t.zchunk = c.zchunk;
+    const int64_t nblk = (int64_t)t.tiles_x * t.tiles_y * ((a.nz + t.zchunk - 1) / t.zchunk);
     if (nblk > 0x7fffffff) return hipErrorInvalidValue;
     constexpr int N = WCount<R, BOX, 3>::value;
     const Wts<N> W = pack_w<N>(BOX ? 1 : 0, 3, R, w);
-    hipLaunchKernelGGL((k_suite3<R, BOX, TY, RY>), dim3((unsigned)nblk), dim3(64 * TY / RY), 0, s, a, t,
-                       W);
+    hipLaunchKernelGGL((k_suite3<R, BOX, TX, NT, RY>), dim3((unsigned)nblk), dim3(NT), 0, s, a, t, W);
     return hipGetLastError();
+}
+
+template <int R, bool BOX>
+hipError_t run3(const float *w, const SuiteArgs &a, hipStream_t s) {
+    // us per plane of each tile (see fastest_sweep), fitted to sweeps of the
+    // tiles and z-splits over 5 grids from 100x91x70 to 512^3.  Each of a
+    // block's 2r start-up planes is computed like any other, so a split is
+    // dear at r = 4 and cheap at r = 1.  The widest tile, split for one block
+    // per CU, had been the only one, at twice the time of a narrower one
+    // where it was half empty (384x320x256: star r = 4 75-96 us against 52,
+    // box r = 1 87 against 44; 100x91x70, r = 4: 15-20 against 9; 512^3 213
+    // both).
+    static const SweepRate rates[5][3] = {
+        {{256, 16, 2, 1, {{0.60, 0.60}, {0.60, 0.60}, {1.25, 1.25}}},       // star r = 1
+         {128, 16, 2, 4, {{0.31, 0.31}, {0.31, 0.50}, {0.70, 0.90}}},
+         {64, 16, 1, 6, {{0.21, 0.25}, {0.21, 0.40}, {0.42, 0.60}}}},
+        {{256, 16, 2, 1, {{0.80, 0.80}, {0.80, 0.80}, {1.38, 1.38}}},       // star r = 2
+         {128, 16, 2, 3, {{0.36, 0.54}, {0.36, 0.60}, {0.76, 0.90}}},
+         {64, 16, 1, 5, {{0.23, 0.35}, {0.23, 0.50}, {0.42, 0.70}}}},
+        {{256, 16, 2, 1, {{1.05, 1.05}, {1.05, 1.05}, {1.45, 1.45}}},       // star r = 3
+         {128, 16, 2, 3, {{0.48, 0.68}, {0.48, 0.75}, {0.78, 1.00}}},
+         {64, 16, 1, 4, {{0.28, 0.44}, {0.28, 0.60}, {0.44, 0.80}}}},
+        {{256, 16, 2, 1, {{1.29, 1.29}, {1.29, 1.29}, {1.52, 1.52}}},       // star r = 4
+         {128, 16, 2, 3, {{0.59, 0.83}, {0.59, 0.95}, {0.81, 1.10}}},
+         {64, 16, 1, 4, {{0.34, 0.53}, {0.34, 0.70}, {0.46, 0.90}}}},
+        {{256, 16, 2, 1, {{1.00, 1.00}, {1.00, 1.00}, {1.49, 1.49}}},       // box r = 1
+         {128, 16, 2, 4, {{0.52, 0.63}, {0.52, 0.70}, {0.73, 0.90}}},
+         {64, 16, 1, 5, {{0.29, 0.40}, {0.29, 0.50}, {0.42, 0.70}}}}};
+    const double start = 1.85 * R;
+    const TileCfg c = fastest_sweep(rates[BOX ? 4 : R - 1], 3, a.nx, a.ny, a.nz, 8, {start, start, start}, 0.0);
+    log_line("sp_apply: %s radius %d, %dx%dx%d -> tile %dx%dx%d, z-chunk %d", BOX ? "box" : "star", R, a.nx, a.ny,
+             a.nz, c.tx, c.ty, c.ry, c.zchunk);
+    switch (c.tx) {
+        case 256: return run3t<R, BOX, 256, 512, 2>(c, w, a, s);
+        case 128: return run3t<R, BOX, 128, 256, 2>(c, w, a, s);
+        default: return run3t<R, BOX, 64, 256, 1>(c, w, a, s);
+    }
+}
+
+// The 2D box of radius 4 is bound by its 81 multiply-adds where the plane is
+// large enough for the matrix kernel's long chunks (rows of 256-point strips:
+// 8192^2 has 262144, 147 us against 179; 5000x4100 82000, 56 against 63;
+// 2174x2965 26685, 25 against 23).
+bool box2r4_on_matrix_cores(const SuiteArgs &a) {
+    return (int64_t)((a.nx + 255) / 256) * a.ny * a.nz >= 50000;
 }
 
 template <bool BOX>
 hipError_t dispatch(int ndim, int radius, const float *w, const SuiteArgs &a, hipStream_t s) {
     if (ndim == 2) {
+        if (BOX && radius == 4 && box2r4_on_matrix_cores(a)) return launch_box2r4(w, a, s);
         switch (radius) {
             case 1: return run2<1, BOX>(w, a, s);
             case 2: return run2<2, BOX>(w, a, s);
