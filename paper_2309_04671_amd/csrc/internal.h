@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <vector>
+
 #include "stencil.h"
 
 namespace sp {
@@ -104,21 +106,20 @@ struct TileCfg {
 struct SweepRate {
     int tx, ty, ry;
     int occ;                 // blocks that share a CU
-    // CU time of one plane of a block and least time of a plane (us), with
-    // the fields in the L2 caches, in the 256 MB behind them, and in HBM
-    struct {
-        double us, lat;
+    // With the fields in the L2 caches, in the 256 MB behind them, and in HBM:
+    struct At {
+        double us, lat;      // CU time of one plane of a block, least time of a plane
+        double start;        // planes' worth of time before a block's first output
+        double block_us;     // time of 256 further blocks
     } at[3];
 };
-// Planes that a block streams before its first output, in planes of its time:
-// one that shares its CU, and one alone on it with the fields cached / in HBM.
-struct SweepStart {
-    double shared, alone, alone_hbm;
-};
 // Tile and z-split of a sweep by expected launch time.  bytes: per point, of
-// all fields the sweep touches; block_us: time of 256 further blocks.
-TileCfg fastest_sweep(const SweepRate *r, int n, int nx, int ny, int nz, int bytes, SweepStart start,
-                      double block_us);
+// all fields the sweep touches.
+TileCfg fastest_sweep(const SweepRate *r, int n, int nx, int ny, int nz, int bytes);
+// Tile and z-split of one leapfrog launch over several grids of a storage type
+// by expected time, with at most max_zchunk planes per block and max_blocks
+// blocks (zchunk 0: no configuration has so few).
+TileCfg choose_tiles_batch(const std::vector<sp_grid> &grids, int max_zchunk, int64_t max_blocks);
 // Launch configuration of the k_star25 sweeps for a grid, storage type and mode.
 TileCfg choose_tiles(int nx, int ny, int nz, int dtype, int mode);
 // Planes per block for `tiles` xy tiles when per_round blocks fill the GPU.

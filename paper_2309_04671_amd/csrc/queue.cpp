@@ -32,15 +32,30 @@ int64_t align256(int64_t b) { return (b + 255) / 256 * 256; }
 // Blocks that record n receivers.
 int rec_blocks(int n) { return (std::max(0, n) + sp::REC_BLOCK - 1) / sp::REC_BLOCK; }
 
-// Planes per block of a shot that shares its launch with other shots.  A
+// Most planes per block of a shot that shares its launch with other shots.  A
 // lone grid is split along z as far as it needs to fill the GPU (a small
-// grid into chunks shorter than this); in a batch the other shots supply
+// grid into chunks shorter than this); in a large batch the other shots supply
 // that parallelism, and short, equal chunks keep the launch's tail short.
-// Measured on a saturating batch of the four served shapes: 16 beats the
-// lone-grid split by 1.8 % in capacity, 8 and 12 lose to the re-read
+// Measured on a saturating batch of four shapes from 64^3 to 192^3: 16 beats
+// the lone-grid split by 1.8 % in capacity, 8 and 12 lose to the re-read
 // start-up planes, 24 and longer to the tail.  A shot alone in its launch
 // keeps its own split.  The z-split never changes a point's arithmetic.
 constexpr int QUEUE_ZCHUNK = 16;
+
+// Shots of one storage type share a launch, on the tile and z-split with the
+// least expected time for all of them, unless they are deep enough to fill the
+// GPU alone (own chunks longer than this): those share one only with shots of
+// their own tile.  A launch per tile leaves a tail per tile and step (8 shots
+// around 160^3 in FP32 and FP16, 32 steps: 4.7 ms in four launches per step, 3.8
+// in two), and a small batch on 16-plane chunks leaves the GPU idle (4
+// shots around 79^3, 22 steps: 1.14 ms, with the split chosen for the batch 0.83).
+constexpr int SHARED_ZCHUNK = 48;
+
+bool same_tile(const sp::TileCfg &a, const sp::TileCfg &b) { return a.tx == b.tx && a.ty == b.ty && a.ry == b.ry; }
+
+int tiles_of(const sp_grid &g, const sp::TileCfg &t) {
+    return ((g.nx + t.tx - 1) / t.tx) * ((g.ny + t.ty - 1) / t.ty);
+}
 
 // Same block -> tile map as the single-grid kernels (contiguous per XCD).
 int xcd_tile_host(int bid, int n) {
@@ -97,7 +112,8 @@ struct Shot {
     sp_grid g, gv;
     sp::TileCfg tile;
     sp::SweepArgs base;          // validated arguments without per-step fields (own z-split)
-    int nblk = 0;                // blocks at the batch z-split (at least those of base)
+    int nblk = 0, nblk_own = 0;  // most blocks in a batch, blocks of base
+    bool shared = false;         // one launch with every such shot of its storage type
     sp::SweepArgs run;           // base with the z-split of the current composition
     int nblk_run = 0;
     int64_t bytes = 0, off = -1;
@@ -169,7 +185,7 @@ int64_t shot_bytes(const sp_grid &g, const sp_grid &gv) {
 int64_t ctrl_need(const std::vector<const Shot *> &set, int k) {
     int64_t blocks = 0, recs = 0;
     for (auto *s : set) {
-        blocks += s->nblk + rec_blocks(s->d.nrec);
+        blocks += (set.size() > 1 ? s->nblk : s->nblk_own) + rec_blocks(s->d.nrec);
         recs += s->d.nrec;
     }
     const int64_t n = (int64_t)set.size();
@@ -202,8 +218,7 @@ int rebuild(sp_queue *q, const std::vector<Shot *> &act, int k) {
         Shot &s = *sp_;
         Group *gp = nullptr;
         for (auto &g : q->groups)
-            if (g.dtype == s.g.dtype && g.tile.tx == s.tile.tx && g.tile.ty == s.tile.ty &&
-                g.tile.ry == s.tile.ry)
+            if (g.dtype == s.g.dtype && g.members[0]->shared == s.shared && (s.shared || same_tile(g.tile, s.tile)))
                 gp = &g;
         if (!gp) {
             q->groups.push_back(Group());
@@ -216,9 +231,26 @@ int rebuild(sp_queue *q, const std::vector<Shot *> &act, int k) {
         gp->nrb += rec_blocks(s.d.nrec);
     }
     for (auto &g : q->groups) {
+        int zchunk = QUEUE_ZCHUNK;
+        if (g.members.size() > 1 && g.members[0]->shared) {
+            // within the blocks that admission counted on
+            std::vector<sp_grid> grids;
+            int64_t most = 0;
+            for (Shot *m : g.members) {
+                grids.push_back(m->g);
+                most += m->nblk;
+            }
+            const sp::TileCfg t = sp::choose_tiles_batch(grids, QUEUE_ZCHUNK, most);
+            if (t.zchunk > 0) {
+                g.tile = t;
+                zchunk = t.zchunk;
+            }
+        }
         for (Shot *m : g.members) {
-            const int zc = g.members.size() > 1 ? std::min(QUEUE_ZCHUNK, m->g.nz) : m->base.zchunk;
+            const int zc = g.members.size() > 1 ? std::min(zchunk, m->g.nz) : m->base.zchunk;
             m->run = m->base;
+            m->run.tiles_x = (m->g.nx + g.tile.tx - 1) / g.tile.tx;
+            m->run.tiles_y = (m->g.ny + g.tile.ty - 1) / g.tile.ty;
             m->run.zchunk = zc;
             m->run.nzc = (m->g.nz + zc - 1) / zc;
             m->nblk_run = m->run.tiles_x * m->run.tiles_y * m->run.nzc;
@@ -612,10 +644,13 @@ int sp_submit(sp_queue *q, const sp_shot_desc *d, uint64_t *ticket) {
                               d->nrec ? &rec : nullptr, &s.base, &s.tile))
         return e;
     {
-        // blocks at the larger of the two z-splits (alone: its own; batched: QUEUE_ZCHUNK)
+        // blocks alone, and at most in a batch (a composition may also leave it alone in its launch)
         const int zb = std::min(QUEUE_ZCHUNK, s.g.nz), zs = s.base.zchunk;
-        s.nblk = s.base.tiles_x * s.base.tiles_y *
-                 std::max((s.g.nz + zb - 1) / zb, (s.g.nz + zs - 1) / zs);
+        s.shared = zs <= SHARED_ZCHUNK && !std::getenv("SP_TILE");     // the override also names a shot's tile
+        s.nblk_own = s.base.tiles_x * s.base.tiles_y * ((s.g.nz + zs - 1) / zs);
+        const int tiles = s.shared ? std::max(tiles_of(s.g, s.tile), tiles_of(s.g, sp::TileCfg{64, 16, 1, 1}))
+                                   : s.base.tiles_x * s.base.tiles_y;
+        s.nblk = std::max(s.nblk_own, tiles * ((s.g.nz + zb - 1) / zb));
     }
     if (!sp::batch_supported(s.tile))
         return fail(SP_EUNSUPPORTED, "sp_submit: tile configuration %dx%dx%d is not batched",

@@ -1287,6 +1287,7 @@ hipError_t launch_batch_cfg(int mode, const TileCfg &t, const SweepArgs *args, c
                             int nblk, hipStream_t s) {
     if (t.tx == 256 && t.ty == 16 && t.ry == 2) return launch_batch_t<256, 16, 2, T>(mode, args, table, nblk, s);
     if (t.tx == 128 && t.ty == 16 && t.ry == 2) return launch_batch_t<128, 16, 2, T>(mode, args, table, nblk, s);
+    if (t.tx == 128 && t.ty == 32 && t.ry == 2) return launch_batch_t<128, 32, 2, T>(mode, args, table, nblk, s);
     if (t.tx == 64 && t.ty == 16 && t.ry == 1) return launch_batch_t<64, 16, 1, T>(mode, args, table, nblk, s);
     if (t.tx == 256 && t.ty == 16 && t.ry == 1) return launch_batch_t<256, 16, 1, T>(mode, args, table, nblk, s);
     return hipErrorInvalidValue;
@@ -1409,16 +1410,22 @@ int occupancy_zchunk(int64_t tiles, int nz, int per_round) {
 // Leapfrog and apply sweeps: tile and z-split by the time a launch is
 // expected to take, over the candidates below and the splits of z into at
 // most 12 chunks or into chunks of at most 32 planes:
-//     (us per plane of the blocks that share a CU, at least the plane's
-//      latency) x (planes per block + start-up) + a cost per block.
-// A tile that has a CU to itself runs in whole rounds of 256 blocks; several
-// small blocks share a CU and fill one another's tails.  The rates are fitted
-// to sweeps of every tile and split over 15 grids from 64^3 to 512^3 on live
-// data, for grids whose fields fit the L2 caches (32 MB) and larger ones.
-// What they come to:
-//  * 256x16 and 128x32 tiles read the least halo but waste what a tile has
-//    past a ragged edge and the CUs past a whole round: 200^3 runs 29.5 us
-//    on 256x16 tiles of 12 planes, 37.6 on three narrow tiles per row;
+//     (time of a plane of the blocks in flight) x (planes per block + start-up)
+//     + a cost per block.
+// A tile that has a CU to itself runs in rounds of 256 blocks; a round that is
+// partly filled takes between a plane's latency and a full round's time, as
+// its blocks have more of the bandwidth each.  Several small blocks share a CU
+// and fill one another's tails.  The rates are fitted to sweeps of every tile
+// and split over 140 to 220 grids from 30^3 to 1024x1024x512 on live data, for
+// fields in the L2 caches (36 MB), in the memory-side cache (240 MB) and in
+// HBM.  On grids left out of a fit the choice is 0.2-1.6 % slower than the
+// best measured one (16 bits in HBM 4 %); whole rounds only, and no 128x32
+// leapfrog tile, had cost 1-4 % and up to 17 %.  What it comes to:
+//  * 128x32 and 256x16 tiles read the least halo; in HBM one round of deep
+//    chunks, whose neighbours stream the same planes at the same time, beats
+//    many shallow ones even with a tenth of the CUs idle: 640x480x700
+//    leapfrog 225 blocks of 234 planes 593 us, 1500 of 35 623, the 256x16
+//    tiles before 665; 510x900x604 apply 228 of 302 470, 1276 of 55 503;
 //  * 64x16 tiles cost half as much again per point, three (FP32) or four
 //    (16 bits) to a CU, and fit any extent: 300x280x200 56 us against 64,
 //    128x120x96 7.5 against 9.1, FP16 at 300x280x200 45 against 56;
@@ -1426,34 +1433,49 @@ int occupancy_zchunk(int64_t tiles, int nz, int per_round) {
 //    (16-bit grids had kept chunks of at least 16 planes: 64^3 18.5 us per
 //    step, 7.6 with 2-plane chunks); a 16-bit block also costs its slab
 //    records (an atomic at the end, dependent loads at the start).
-TileCfg fastest_sweep(const SweepRate *r, int n, int nx, int ny, int nz, int bytes, SweepStart start_up,
-                      double block_us) {
-    const double total = (double)nx * ny * nz * bytes;
-    const int where = total < 36e6 ? 0 : total < 240e6 ? 1 : 2;
+namespace {
+
+// Where the fields of a sweep over `bytes` bytes are (index of SweepRate::at).
+int level_of(double bytes) { return bytes < 36e6 ? 0 : bytes < 240e6 ? 1 : 2; }
+
+// Expected time of nblk blocks of at most zc planes.  Integer rounding: this
+// runs in every call, and with floating-point ceilings it was a microsecond
+// of a 10 us call.
+inline double launch_us(int occ, const SweepRate::At &at, int64_t nblk, int zc) {
+    const double cu = at.us * (1.0 / 256);
+    double plane;
+    if (occ == 1) {
+        const int64_t last = nblk & 255;
+        plane = cu * (double)(nblk - last) + (last ? at.lat + (cu - at.lat * (1.0 / 256)) * (double)last : 0.0);
+    } else {
+        const int64_t slots = 256 * occ;
+        int64_t units = (nblk + 255) & ~(int64_t)255;
+        if (nblk > slots) {
+            // the last round is shared out, and costs about a third of the
+            // slots it leaves empty
+            const int64_t full = nblk < ((int64_t)1 << 31)
+                                     ? (int64_t)((unsigned)(nblk + slots - 1) / (unsigned)slots) * slots
+                                     : (nblk + slots - 1) / slots * slots;
+            units = nblk + (full - nblk) * 45 / 128;
+        }
+        plane = std::max(cu * (double)units, at.lat);
+    }
+    return plane * (zc + at.start) + at.block_us * (1.0 / 256) * (double)nblk;
+}
+
+}  // namespace
+
+TileCfg fastest_sweep(const SweepRate *r, int n, int nx, int ny, int nz, int bytes) {
+    const int where = level_of((double)nx * ny * nz * bytes);
     TileCfg best = {};
     double least = -1.0;
     for (int i = 0; i < n; ++i) {
         const int64_t tiles = (int64_t)((nx + r[i].tx - 1) / r[i].tx) * ((ny + r[i].ty - 1) / r[i].ty);
         const int occ = r[i].occ;
-        const double us = r[i].at[where].us, lat = r[i].at[where].lat;
-        const double start = occ > 1 ? start_up.shared : where == 2 ? start_up.alone_hbm : start_up.alone;
-        // integer rounding throughout: this runs in every call, and with
-        // floating-point ceilings it was a microsecond of a 10 us call
-        const int64_t slots = 256 * occ;
+        const SweepRate::At at = r[i].at[where];
         auto consider = [&](int chunks) {
             const int zc = (int)((unsigned)(nz + chunks - 1) / (unsigned)chunks);
-            const int64_t nblk = tiles * chunks;
-            int64_t units = (nblk + 255) & ~(int64_t)255;     // 256 blocks per CU-filling round
-            if (occ > 1 && nblk > slots) {
-                // several blocks per CU: the last round is shared out, and
-                // costs about a third of the slots it leaves empty
-                const int64_t full = nblk < ((int64_t)1 << 31)
-                                         ? (int64_t)((unsigned)(nblk + slots - 1) / (unsigned)slots) * slots
-                                         : (nblk + slots - 1) / slots * slots;
-                units = nblk + (full - nblk) * 45 / 128;
-            }
-            const double t = std::max((double)units * us * (1.0 / 256), lat) * (zc + start) +
-                             block_us * (1.0 / 256) * (double)nblk;
+            const double t = launch_us(occ, at, tiles * chunks, zc);
             if (least < 0 || t < least) {
                 least = t;
                 best.tx = r[i].tx;
@@ -1469,22 +1491,49 @@ TileCfg fastest_sweep(const SweepRate *r, int n, int nx, int ny, int nz, int byt
     return best;
 }
 
+// Rates of fastest_sweep: FP32 leapfrog, FP32 apply, 16-bit leapfrog.
+constexpr SweepRate WAVE32[3] = {
+    {128, 32, 2, 1, {{1.46, 1.43, 1.89, 0.04}, {2.02, 1.66, 2.13, 2.34}, {2.25, 1.50, 6.00, 3.00}}},
+    {256, 16, 2, 1, {{1.61, 1.47, 0.81, 0.01}, {1.92, 1.92, 1.76, 0.10}, {2.14, 1.47, 6.00, 2.92}}},
+    {64, 16, 1, 3, {{0.59, 1.26, 0.80, 0.08}, {0.79, 1.24, 0.10, 0.81}, {0.63, 1.89, 5.24, 2.97}}}};
+constexpr SweepRate APPLY32[3] = {
+    {128, 32, 2, 1, {{1.10, 1.10, 4.00, 0.00}, {1.51, 1.25, 1.29, 2.33}, {1.30, 1.30, 6.00, 3.00}}},
+    {256, 16, 2, 1, {{1.20, 1.20, 4.00, 0.00}, {1.62, 1.62, 2.42, 0.15}, {1.52, 1.52, 6.00, 0.02}}},
+    {64, 16, 1, 4, {{0.27, 0.42, 0.70, 0.00}, {0.45, 1.39, 0.11, 1.31}, {0.40, 1.26, 0.76, 2.96}}}};
+constexpr SweepRate WAVE16[2] = {
+    {128, 16, 2, 3, {{0.80, 1.27, 1.12, 1.48}, {1.13, 2.62, 0.49, 0.75}, {0.90, 2.40, 0.70, 1.00}}},
+    {64, 16, 1, 4, {{0.32, 0.81, 0.92, 2.33}, {0.44, 1.50, 1.15, 1.89}, {0.48, 2.00, 0.70, 1.00}}}};
+
+TileCfg choose_tiles_batch(const std::vector<sp_grid> &grids, int max_zchunk, int64_t max_blocks) {
+    const bool f32 = grids[0].dtype == SP_F32;
+    const SweepRate *r = f32 ? WAVE32 : WAVE16;
+    double bytes = 0.0;
+    for (const auto &g : grids) bytes += (double)g.nx * g.ny * g.nz * (f32 ? 16 : 10);
+    const int where = level_of(bytes);
+    TileCfg best = {};
+    double least = -1.0;
+    for (int i = 0; i < (f32 ? 3 : 2); ++i) {
+        for (int zc = max_zchunk; zc >= 1; zc -= zc > 8 ? 2 : 1) {
+            int64_t nblk = 0;
+            for (const auto &g : grids)
+                nblk += (int64_t)((g.nx + r[i].tx - 1) / r[i].tx) * ((g.ny + r[i].ty - 1) / r[i].ty) *
+                        ((g.nz + zc - 1) / zc);
+            const double t = launch_us(r[i].occ, r[i].at[where], nblk, zc);
+            if (nblk <= max_blocks && (least < 0 || t < least)) {
+                least = t;
+                best = TileCfg{r[i].tx, r[i].ty, r[i].ry, zc};
+            }
+        }
+    }
+    if (f32 && best.tx == 256) best.ry = 1;
+    return best;
+}
+
 TileCfg choose_tiles(int nx, int ny, int nz, int dtype, int mode) {
-    static const SweepRate r32[3] = {{256, 16, 2, 1, {{1.30, 1.30}, {1.95, 1.95}, {2.75, 2.75}}},
-                                     {128, 16, 2, 2, {{0.90, 1.27}, {1.24, 2.00}, {1.52, 2.20}}},
-                                     {64, 16, 1, 3, {{0.47, 0.70}, {0.70, 1.30}, {0.82, 1.60}}}};
-    static const SweepRate rap[3] = {{128, 32, 2, 1, {{1.10, 1.10}, {1.25, 1.25}, {1.45, 1.45}}},
-                                     {256, 16, 2, 1, {{1.20, 1.20}, {1.28, 1.28}, {1.53, 1.53}}},
-                                     {64, 16, 1, 4, {{0.27, 0.42}, {0.49, 0.80}, {0.46, 0.90}}}};
-    static const SweepRate r16[2] = {{128, 16, 2, 3, {{0.60, 1.00}, {0.88, 2.00}, {0.90, 2.40}}},
-                                     {64, 16, 1, 4, {{0.30, 0.50}, {0.42, 1.45}, {0.48, 2.00}}}};
     if (mode == MODE_WAVE || mode == MODE_APPLY) {
-        // The planes streamed ahead of a chunk cost hardly more than a
-        // latency, which other blocks on the CU hide; for a block alone on
-        // its CU their memory traffic too (half of an apply sweep's is u).
-        TileCfg t = dtype != SP_F32       ? fastest_sweep(r16, 2, nx, ny, nz, 10, {0.7, 0.7, 2.0}, 1.0)
-                    : mode == MODE_APPLY ? fastest_sweep(rap, 3, nx, ny, nz, 8, {0.7, 4.0, 4.0}, 0.0)
-                                         : fastest_sweep(r32, 3, nx, ny, nz, 16, {0.7, 0.7, 2.0}, 0.0);
+        TileCfg t = dtype != SP_F32       ? fastest_sweep(WAVE16, 2, nx, ny, nz, 10)
+                    : mode == MODE_APPLY ? fastest_sweep(APPLY32, 3, nx, ny, nz, 8)
+                                         : fastest_sweep(WAVE32, 3, nx, ny, nz, 16);
         // Short chunks of the FP32 leapfrog hide more latency with four
         // waves per SIMD (1024-thread blocks, one row per thread) than with
         // two: 256^3 360 against 347 GPts/s, 512x300x256 107 against 110 us,
@@ -1535,7 +1584,7 @@ hipError_t launch_sweep_boxes(int mode, const BoxSet &bs, hipStream_t s) {
 
 bool batch_supported(const TileCfg &t) {
     return (t.tx == 256 && t.ty == 16 && (t.ry == 2 || t.ry == 1)) ||
-           (t.tx == 128 && t.ty == 16 && t.ry == 2) || (t.tx == 64 && t.ty == 16 && t.ry == 1);
+           (t.tx == 128 && (t.ty == 16 || t.ty == 32) && t.ry == 2) || (t.tx == 64 && t.ty == 16 && t.ry == 1);
 }
 
 hipError_t launch_sweep(int mode, int dtype, const TileCfg &t, const SweepArgs &a, hipStream_t s) {

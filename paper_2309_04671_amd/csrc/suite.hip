@@ -358,8 +358,8 @@ hipError_t run3t(const TileCfg &c, const float *w, const SuiteArgs &a, hipStream
 
 template <int R, bool BOX>
 hipError_t run3(const float *w, const SuiteArgs &a, hipStream_t s) {
-    // us per plane of each tile (see fastest_sweep), fitted to sweeps of the
-    // tiles and z-splits over 5 grids from 100x91x70 to 512^3.  Each of a
+    // Rates of each tile (see fastest_sweep), fitted to sweeps of the tiles
+    // and z-splits over 76 grids from 30x50x60 to 640x640x500.  Each of a
     // block's 2r start-up planes is computed like any other, so a split is
     // dear at r = 4 and cheap at r = 1.  The widest tile, split for one block
     // per CU, had been the only one, at twice the time of a narrower one
@@ -367,23 +367,27 @@ hipError_t run3(const float *w, const SuiteArgs &a, hipStream_t s) {
     // box r = 1 87 against 44; 100x91x70, r = 4: 15-20 against 9; 512^3 213
     // both).
     static const SweepRate rates[5][3] = {
-        {{256, 16, 2, 1, {{0.60, 0.60}, {0.60, 0.60}, {1.25, 1.25}}},       // star r = 1
-         {128, 16, 2, 4, {{0.31, 0.31}, {0.31, 0.50}, {0.70, 0.90}}},
-         {64, 16, 1, 6, {{0.21, 0.25}, {0.21, 0.40}, {0.42, 0.60}}}},
-        {{256, 16, 2, 1, {{0.80, 0.80}, {0.80, 0.80}, {1.38, 1.38}}},       // star r = 2
-         {128, 16, 2, 3, {{0.36, 0.54}, {0.36, 0.60}, {0.76, 0.90}}},
-         {64, 16, 1, 5, {{0.23, 0.35}, {0.23, 0.50}, {0.42, 0.70}}}},
-        {{256, 16, 2, 1, {{1.05, 1.05}, {1.05, 1.05}, {1.45, 1.45}}},       // star r = 3
-         {128, 16, 2, 3, {{0.48, 0.68}, {0.48, 0.75}, {0.78, 1.00}}},
-         {64, 16, 1, 4, {{0.28, 0.44}, {0.28, 0.60}, {0.44, 0.80}}}},
-        {{256, 16, 2, 1, {{1.29, 1.29}, {1.29, 1.29}, {1.52, 1.52}}},       // star r = 4
-         {128, 16, 2, 3, {{0.59, 0.83}, {0.59, 0.95}, {0.81, 1.10}}},
-         {64, 16, 1, 4, {{0.34, 0.53}, {0.34, 0.70}, {0.46, 0.90}}}},
-        {{256, 16, 2, 1, {{1.00, 1.00}, {1.00, 1.00}, {1.49, 1.49}}},       // box r = 1
-         {128, 16, 2, 4, {{0.52, 0.63}, {0.52, 0.70}, {0.73, 0.90}}},
-         {64, 16, 1, 5, {{0.29, 0.40}, {0.29, 0.50}, {0.42, 0.70}}}}};
-    const double start = 1.85 * R;
-    const TileCfg c = fastest_sweep(rates[BOX ? 4 : R - 1], 3, a.nx, a.ny, a.nz, 8, {start, start, start}, 0.0);
+        // star r = 1
+        {{256, 16, 2, 1, {{1.30, 0.60, 4.69, 0.04}, {1.17, 0.48, 0.09, 0.16}, {1.10, 1.10, 5.81, 0.15}}},
+         {128, 16, 2, 4, {{0.49, 0.73, 1.01, 0.26}, {0.56, 1.25, 0.05, 0.93}, {0.63, 0.99, 5.17, 0.40}}},
+         {64, 16, 1, 6, {{0.24, 0.83, 1.01, 0.32}, {0.40, 2.38, 0.13, 1.34}, {0.45, 2.57, 0.32, 0.55}}}},
+        // star r = 2
+        {{256, 16, 2, 1, {{1.00, 0.77, 3.64, 0.06}, {1.24, 1.24, 1.26, 0.36}, {1.36, 1.21, 9.00, 3.00}}},
+         {128, 16, 2, 3, {{0.47, 1.05, 3.40, 0.04}, {0.60, 1.31, 0.07, 1.35}, {0.80, 1.63, 5.49, 1.79}}},
+         {64, 16, 1, 5, {{0.30, 0.78, 0.55, 1.04}, {0.40, 1.23, 0.05, 0.51}, {0.59, 1.39, 0.05, 0.46}}}},
+        // star r = 3
+        {{256, 16, 2, 1, {{1.35, 1.28, 8.50, 0.70}, {1.26, 0.91, 4.03, 0.50}, {1.45, 1.45, 5.55, 0.00}}},
+         {128, 16, 2, 3, {{0.51, 0.93, 5.52, 0.35}, {0.73, 1.53, 0.50, 1.52}, {0.78, 1.00, 5.55, 0.00}}},
+         {64, 16, 1, 4, {{0.36, 0.89, 1.01, 1.22}, {0.45, 1.41, 0.12, 0.82}, {0.44, 0.80, 5.55, 0.00}}}},
+        // star r = 4
+        {{256, 16, 2, 1, {{2.44, 2.00, 3.50, 0.20}, {1.57, 1.55, 8.72, 3.00}, {1.52, 1.52, 7.40, 0.00}}},
+         {128, 16, 2, 3, {{0.65, 1.66, 5.46, 0.77}, {0.68, 1.42, 3.19, 0.17}, {0.81, 1.10, 7.40, 0.00}}},
+         {64, 16, 1, 4, {{0.40, 0.61, 2.28, 0.89}, {0.44, 0.99, 0.16, 0.72}, {0.46, 0.90, 7.40, 0.00}}}},
+        // box r = 1
+        {{256, 16, 2, 1, {{1.44, 0.68, 4.90, 0.85}, {1.57, 1.57, 0.59, 0.02}, {1.39, 1.08, 0.20, 0.37}}},
+         {128, 16, 2, 4, {{0.80, 1.67, 1.66, 0.07}, {0.57, 1.20, 0.23, 1.62}, {0.51, 0.74, 5.55, 2.75}}},
+         {64, 16, 1, 5, {{0.39, 1.02, 0.21, 1.16}, {0.33, 1.44, 0.11, 0.80}, {0.37, 0.88, 0.25, 0.09}}}}};
+    const TileCfg c = fastest_sweep(rates[BOX ? 4 : R - 1], 3, a.nx, a.ny, a.nz, 8);
     log_line("sp_apply: %s radius %d, %dx%dx%d -> tile %dx%dx%d, z-chunk %d", BOX ? "box" : "star", R, a.nx, a.ny,
              a.nz, c.tx, c.ty, c.ry, c.zchunk);
     switch (c.tx) {
