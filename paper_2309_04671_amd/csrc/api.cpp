@@ -590,6 +590,13 @@ int sp_wave_step_pml(const sp_grid *g, const sp_coeffs *c, double dt, double dx,
     };
     Box boxes[7];
     int nb = 0;
+    // Small tiles of 4-plane blocks (3 in the x slabs) where the layer fills
+    // their rows and its slabs do not fill the GPU for long: of 14 grids with
+    // W = 32 up to 30 M layer cells 11 run 3-48 % faster, one 5 % slower; with W
+    // = 8 and 16 (half-empty x tiles) 7 of 16 are slower, and 1024x1024x512 (107
+    // M) runs 1.95 ms against 2.13.
+    const bool small_shell = dec == SP_PML_TWO && W >= 24 &&
+                             (int64_t)nx * ny * nz - (int64_t)(nx - 2 * W) * (ny - 2 * W) * (nz - 2 * W) < 30000000;
     auto add = [&](int x0, int x1, int y0, int y1, int z0, int z1, int mode, bool wide) {
         Box &b = boxes[nb++];
         b.mode = mode;
@@ -611,11 +618,11 @@ int sp_wave_step_pml(const sp_grid *g, const sp_coeffs *c, double dt, double dx,
         }
         b.t = sp::choose_tiles(b.a.nx, b.a.ny, b.a.nz, SP_F32, mode);
         if (dec == SP_PML_TWO && mode == sp::MODE_PML) {
-            // the shell as one launch of 512-thread blocks (one per CU):
-            // the z and y slabs on 256x8x1 tiles, the x slabs on 32x64x1
-            // (their z-chunks: split_shell, once every slab is known)
-            b.t.tx = wide ? 256 : 32;
-            b.t.ty = wide ? 8 : 64;
+            // the shell as one launch (see k_star25_shell): the z and y slabs
+            // on 256x8x1 tiles, the x slabs on 32x64x1 (their z-chunks:
+            // split_shell, once every slab is known), or on small tiles
+            b.t.tx = wide ? small_shell ? 64 : 256 : 32;
+            b.t.ty = wide ? small_shell ? 16 : 8 : small_shell ? 32 : 64;
             b.t.ry = 1;
         }
         fill_tiling(b.a, b.t);
@@ -644,6 +651,14 @@ int sp_wave_step_pml(const sp_grid *g, const sp_coeffs *c, double dt, double dx,
     // 310 -> 222 us; 250x230x200, W = 16: 79 -> 73; 300x700x333, W = 32: 571
     // -> 398; 512^3, W = 16: 633 -> 589; 1024x1024x512, W = 32: 1967 both.
     auto split_shell = [&] {
+        if (small_shell) {
+            for (int q = 1; q < nb; ++q) {
+                const int most = boxes[q].wide ? 4 : 3, chunks = (boxes[q].a.nz + most - 1) / most;
+                boxes[q].t.zchunk = (boxes[q].a.nz + chunks - 1) / chunks;
+                fill_tiling(boxes[q].a, boxes[q].t);
+            }
+            return;
+        }
         auto chunk = [&](const Box &b, int l) {
             if (l == 0) return sp::occupancy_zchunk((int64_t)b.a.tiles_x * b.a.tiles_y, b.a.nz, 256);
             const int most = b.wide ? l : 3 * l / 4, chunks = (b.a.nz + most - 1) / most;
@@ -708,6 +723,7 @@ int sp_wave_step_pml(const sp_grid *g, const sp_coeffs *c, double dt, double dx,
             err = sp::launch_sweep(boxes[0].mode, SP_F32, boxes[0].t, boxes[0].a, s);
             sp::BoxSet shell;
             shell.n = nb - 1;
+            shell.small = small_shell;
             shell.first[0] = 0;
             for (int q = 1; q < nb; ++q) {
                 const sp::SweepArgs &ba = boxes[q].a;

@@ -125,16 +125,17 @@ TileCfg choose_tiles(int nx, int ny, int nz, int dtype, int mode);
 // Planes per block for `tiles` xy tiles when per_round blocks fill the GPU.
 int occupancy_zchunk(int64_t tiles, int nz, int per_round);
 
-// Up to MAX_BOXES boxes of one grid swept by one launch of 512-thread
-// blocks: box k takes blocks [first[k], first[k+1]), on 256x8x1 tiles if
-// wide[k], else on 32x64x1 tiles (kernel arguments: 6 x 544 B fits the
-// 4 KB limit).
+// Up to MAX_BOXES boxes of one grid swept by one launch: box k takes blocks
+// [first[k], first[k+1]), on 256x8x1 tiles if wide[k], else on 32x64x1 tiles
+// (512 threads), or if `small` on 64x16x1 and 32x32x1 tiles (256 threads;
+// kernel arguments: 6 x 544 B fits the 4 KB limit).
 constexpr int MAX_BOXES = 6;
 struct BoxSet {
     SweepArgs a[MAX_BOXES];
     int first[MAX_BOXES + 1];
     int wide[MAX_BOXES];
     int n;
+    bool small;
 };
 hipError_t launch_sweep_boxes(int mode, const BoxSet &bs, hipStream_t s);
 // Configurations the batched (multi-grid) sweep is compiled for.

@@ -642,8 +642,12 @@ __device__ __forceinline__ void star25_body(const SweepArgs &a, const int lin) {
     }
     // halo chunks of planes z .. z+HD-1; the FP32 leapfrog, gradient and
     // energy sweeps on 1024-thread blocks (a 128-VGPR budget) and the fused
-    // adjoint (two fields) keep depth 1
-    constexpr int HD = ((NT > 512 && MODE != MODE_APPLY && std::is_same<T, float>::value) || TWO) ? 1 : HQ;
+    // adjoint (two fields) keep depth 1, the layer's 256-thread blocks depth 2
+    // (189 -> 162 VGPRs with its x neighbours of eta as scalars: three waves
+    // per SIMD)
+    constexpr int HD = ((NT > 512 && MODE != MODE_APPLY && std::is_same<T, float>::value) || TWO) ? 1
+                       : MODE == MODE_PML && NT == 256                                           ? 2
+                                                                                                 : HQ;
     raw hq[HPT][HD];
 #pragma unroll
     for (int j = 0; j < HPT; ++j)
@@ -696,22 +700,23 @@ __device__ __forceinline__ void star25_body(const SweepArgs &a, const int lin) {
     double esum = 0.0;                    // MODE_ENERGY: this thread's partial sum
 
     // MODE_PML (one row per thread): damping eta as a 3-plane queue of the
-    // own chunk (planes z-1, z, z+1) plus the x/y-neighbour chunks of plane
-    // z (x-4, x+4, y-1, y+1); psi of plane z.  All fetched one plane ahead
+    // own chunk (planes z-1, z, z+1) plus its x neighbours and y-neighbour
+    // chunks of plane z (x-1, x+4, y-1, y+1); psi of plane z.  All fetched one plane ahead
     // from offsets that are valid for every lane.
-    f4v eq[3], ex[4], ps;
+    f4v eq[3], ey[2], ps;
+    float exl, exr;
     const int64_t ve = st_ok[0] ? vown[0] : 0, pe = st_ok[0] ? own[0] : 0;
-    auto eta_xy = [&](int zz, f4v *d) {
+    auto eta_xy = [&](int zz, f4v *d, float &l, float &r) {
         const float *e = a.eta + (int64_t)zz * a.vsz + ve;
-        d[0] = ld4(e - 4);
-        d[1] = ld4(e + 4);
-        d[2] = ld4(e - a.vsy);
-        d[3] = ld4(e + a.vsy);
+        l = e[-1];
+        r = e[4];
+        d[0] = ld4(e - a.vsy);
+        d[1] = ld4(e + a.vsy);
     };
     if constexpr (MODE == MODE_PML) {
 #pragma unroll
         for (int k = 0; k < 3; ++k) eq[k] = ld4(a.eta + (int64_t)(zb - 1 + k) * a.vsz + ve);
-        eta_xy(zb, ex);
+        eta_xy(zb, ey, exl, exr);
         ps = ld4(a.psi + (int64_t)zb * sz + pe);
     }
 
@@ -795,11 +800,12 @@ __device__ __forceinline__ void star25_body(const SweepArgs &a, const int lin) {
                     hn2[j] = h_ok[j] ? ld4(a.u2 + (int64_t)(z + 1) * sz + hoff[j]) : zero;
             }
         }
-        f4v eq_n, ex_n[4], ps_n;
+        f4v eq_n, ey_n[2], ps_n;
+        float exl_n = 0.f, exr_n = 0.f;
         if constexpr (MODE == MODE_PML) {
             // planes z+2 (<= nz+1) and z+1 always lie in the frame
             eq_n = ld4(a.eta + (int64_t)(z + 2) * a.vsz + ve);
-            eta_xy(z + 1, ex_n);
+            eta_xy(z + 1, ey_n, exl_n, exr_n);
             ps_n = ld4(a.psi + (int64_t)(z + 1) * sz + pe);
         }
 
@@ -902,8 +908,8 @@ __device__ __forceinline__ void star25_body(const SweepArgs &a, const int lin) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const float ux = (i < 3 ? ctr[i + 1] : R[0]) - (i > 0 ? ctr[i - 1] : L[3]);
-                    const float ex1 = (i < 3 ? eC[i + 1] : ex[1][0]) - (i > 0 ? eC[i - 1] : ex[0][3]);
-                    const float G = 0.25f * (ex1 * ux + (ex[3][i] - ex[2][i]) * (yrow[j + 5][i] - yrow[j + 3][i]) +
+                    const float ex1 = (i < 3 ? eC[i + 1] : exr) - (i > 0 ? eC[i - 1] : exl);
+                    const float G = 0.25f * (ex1 * ux + (ey[1][i] - ey[0][i]) * (yrow[j + 5][i] - yrow[j + 3][i]) +
                                              (eq[2][i] - eq[0][i]) * (q[j][5][i] - q[j][3][i]));
                     const float ae = eC[i] * a.dt;
                     const float bb = ae + a.alpha_dt;
@@ -1040,8 +1046,10 @@ __device__ __forceinline__ void star25_body(const SweepArgs &a, const int lin) {
             eq[0] = eq[1];
             eq[1] = eq[2];
             eq[2] = eq_n;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) ex[k] = ex_n[k];
+            ey[0] = ey_n[0];
+            ey[1] = ey_n[1];
+            exl = exl_n;
+            exr = exr_n;
             ps = ps_n;
         }
 #pragma unroll
@@ -1112,20 +1120,25 @@ k_star25(SweepArgs a) {
 // Several boxes of one grid in one launch (the absorbing layer's shell as
 // one region): block b sweeps tile b - first[k] of box k, the box whose
 // block range holds b; each XCD receives one contiguous range of blocks.
-// The wide z and y slabs run on 256x8x1 tiles and the 32-wide x slabs on
-// 32x64x1 tiles (both 512 threads; the choice is uniform per block), so the
-// thin x slabs overlap the wide ones.
-template <int MODE, typename T>
-__global__ void __launch_bounds__(512) k_star25_shell(const BoxSet bs) {
+// The wide z and y slabs run on WXxWY tiles and the 32-wide x slabs on 32xNY
+// tiles (NT threads both; the choice is uniform per block), so the thin x
+// slabs overlap the wide ones.  512-thread blocks have a CU each (212 VGPRs);
+// the 256-thread ones keep a shallower halo queue (162 VGPRs), and three share
+// a CU and hide each other's start-up.  With 4-plane blocks and W = 32, per
+// step with the inner box: 448x384x256 214 -> 210 us, 140x300x210 89 -> 76,
+// 279x459x87 117 -> 77, 323x283x407 226 -> 210.
+template <int WX, int WY, int NY, int NT, int MODE, typename T>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 256 ? 3 : 1)))
+k_star25_shell(const BoxSet bs) {
     const int lin = xcd_tile(blockIdx.x, gridDim.x);
     int k = 0;
 #pragma unroll
     for (int i = 1; i < MAX_BOXES; ++i)
         if (i < bs.n && lin >= bs.first[i]) k = i;
     if (bs.wide[k])
-        star25_body<256, 8, 1, MODE, T>(bs.a[k], lin - bs.first[k]);
+        star25_body<WX, WY, 1, MODE, T>(bs.a[k], lin - bs.first[k]);
     else
-        star25_body<32, 64, 1, MODE, T>(bs.a[k], lin - bs.first[k]);
+        star25_body<32, NY, 1, MODE, T>(bs.a[k], lin - bs.first[k]);
 }
 
 // Batched form: block b computes tile table[b].y of grid table[b].x, whose
@@ -1578,7 +1591,11 @@ TileCfg choose_tiles(int nx, int ny, int nz, int dtype, int mode) {
 
 hipError_t launch_sweep_boxes(int mode, const BoxSet &bs, hipStream_t s) {
     if (mode != MODE_PML || bs.n < 1 || bs.n > MAX_BOXES) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_star25_shell<MODE_PML, float>), dim3(bs.first[bs.n]), dim3(512), 0, s, bs);
+    const dim3 grid(bs.first[bs.n]);
+    if (bs.small)
+        hipLaunchKernelGGL((k_star25_shell<64, 16, 32, 256, MODE_PML, float>), grid, dim3(256), 0, s, bs);
+    else
+        hipLaunchKernelGGL((k_star25_shell<256, 8, 64, 512, MODE_PML, float>), grid, dim3(512), 0, s, bs);
     return hipGetLastError();
 }
 
