@@ -179,6 +179,13 @@ hipError_t launch_sweep_batch(int mode, int dtype, const TileCfg &t, const Sweep
 // Batched receivers: thread r records receiver rmap[r].y of grid rmap[r].x.
 hipError_t launch_record_batch(int dtype, const RecArgs *recs, const int2 *rmap, int total,
                                hipStream_t s);
+// out[i] = *flag[i] for n <= MAX_FLAGS device words; out: device-visible host
+// memory, complete once an event after the launch has completed.
+constexpr int MAX_FLAGS = 64;
+struct FlagSet {
+    const uint32_t *flag[MAX_FLAGS];
+};
+hipError_t launch_gather_flags(const FlagSet &f, int n, uint32_t *out, hipStream_t s);
 // Interior-dense FP32 [nz][ny][nx] <-> field at interior origin.
 hipError_t launch_pack(const float *dense, float *field, int64_t sy, int64_t sz, int nx, int ny,
                        int nz, hipStream_t s);

@@ -169,6 +169,7 @@ struct sp_queue {
     int comp_k = 0;
     std::vector<Group> groups;
     int64_t dyn_off = 0, dyn_bytes = 0;  // per-chunk region of the control part
+    bool tables_new = false;             // the static region before it is not uploaded yet
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
 };
@@ -209,8 +210,9 @@ void destroy_graph(sp_queue *q) {
     q->graph = nullptr;
 }
 
-// Lay out the control part for the active set and k steps per chunk and
-// upload the static tables (the chunk graph is captured by the first chunk).
+// Lay out the control part for the active set and k steps per chunk and fill
+// its static tables (the first chunk uploads them with its own arguments and
+// captures the chunk graph).
 int rebuild(sp_queue *q, const std::vector<Shot *> &act, int k) {
     destroy_graph(q);
     q->groups.clear();
@@ -265,7 +267,6 @@ int rebuild(sp_queue *q, const std::vector<Shot *> &act, int k) {
         g.off_rmap = off;
         off += align256((int64_t)g.nrec * 8);
     }
-    const int64_t static_end = off;
     q->dyn_off = off;
     for (auto &g : q->groups) {
         g.off_args = off;
@@ -303,10 +304,7 @@ int rebuild(sp_queue *q, const std::vector<Shot *> &act, int k) {
         for (size_t m = 0; m < g.members.size(); ++m)
             for (int i = 0; i < g.members[m]->d.nrec; ++i) rmap[r++] = make_int2((int)m, i);
     }
-    if (static_end > 0) {
-        hipError_t e = hipMemcpyAsync(q->ctrl_dev, q->pinned, static_end, hipMemcpyHostToDevice, q->stream);
-        if (e != hipSuccess) return fail(SP_EDEVICE, "queue: table upload: %s", hipGetErrorString(e));
-    }
+    q->tables_new = true;
     return SP_OK;
 }
 
@@ -389,32 +387,39 @@ int run_chunk(sp_queue *q, int k) {
         }
     }
     hipError_t e = hipSuccess;
-    if (q->dyn_bytes > 0)
-        e = hipMemcpyAsync(q->ctrl_dev + q->dyn_off, q->pinned + q->dyn_off, q->dyn_bytes,
-                           hipMemcpyHostToDevice, q->stream);
+    const int64_t from = q->tables_new ? 0 : q->dyn_off, upto = q->dyn_off + q->dyn_bytes;
+    if (upto > from)
+        e = hipMemcpyAsync(q->ctrl_dev + from, q->pinned + from, upto - from, hipMemcpyHostToDevice, q->stream);
+    q->tables_new = false;
     // A composition's first chunk is launched directly and its graph
     // captured while that chunk runs; later chunks of the same composition
-    // replay the graph.  Short-lived compositions never pay for a capture
-    // on the critical path.
+    // replay the graph.  A composition that ends with this chunk is not
+    // captured: on small shots the capture outlasts the chunk.
     bool capture = false;
+    int64_t left = INT64_MAX;
+    for (auto &g : q->groups)
+        for (Shot *m : g.members) left = std::min<int64_t>(left, m->d.nsteps - m->step);
     if (e == hipSuccess) {
         if (q->exec) {
             e = hipGraphLaunch(q->exec, q->stream);
         } else {
             e = launch_steps(q, k, q->stream);
-            capture = !q->eager;
+            capture = !q->eager && left >= 2 * k;
         }
     }
     if (e == hipSuccess && capture) capture_chunk(q, k);
     // the resident shots' non-finite flags, read back with the chunk
     int nflag = 0;
+    sp::FlagSet fs;
     for (auto &g : q->groups)
         for (Shot *m : g.members) {
-            if (e == hipSuccess)
-                e = hipMemcpyAsync(q->flags_host + nflag, m->nonfinite, sizeof(uint32_t),
-                                   hipMemcpyDeviceToHost, q->stream);
-            ++nflag;
+            fs.flag[nflag++ % sp::MAX_FLAGS] = m->nonfinite;
+            if (e == hipSuccess && nflag % sp::MAX_FLAGS == 0)
+                e = sp::launch_gather_flags(fs, sp::MAX_FLAGS, q->flags_host + nflag - sp::MAX_FLAGS, q->stream);
         }
+    if (e == hipSuccess)
+        e = sp::launch_gather_flags(fs, nflag % sp::MAX_FLAGS, q->flags_host + nflag - nflag % sp::MAX_FLAGS,
+                                    q->stream);
     if (e == hipSuccess) e = hipEventRecord(q->chunk_done, q->stream);
     if (e == hipSuccess) e = hipEventSynchronize(q->chunk_done);
     if (e != hipSuccess) return fail(SP_EDEVICE, "queue: chunk failed: %s", hipGetErrorString(e));
@@ -428,11 +433,8 @@ int run_chunk(sp_queue *q, int k) {
 int init_shot(sp_queue *q, Shot &s) {
     if (q->fake) return SP_OK;
     hipError_t e = hipStreamWaitEvent(q->stream, s.ready, 0);
-    if (e == hipSuccess) e = hipMemsetAsync(s.f0, 0, s.g.bytes, q->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(s.f1, 0, s.g.bytes, q->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(s.v, 0, s.gv.bytes, q->stream);
-    if (e == hipSuccess && s.meta) e = hipMemsetAsync(s.meta, 0, sp_wave_meta_bytes(&s.g), q->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(s.nonfinite, 0, sizeof(uint32_t), q->stream);
+    // fields, velocity, records and flag are one range of the arena
+    if (e == hipSuccess) e = hipMemsetAsync(s.f0, 0, s.bytes, q->stream);
     if (e == hipSuccess)
         e = sp::launch_pack(s.d.v, s.v + s.gv.origin, s.gv.pitch_x, s.gv.pitch_x * s.gv.pitch_y,
                             s.gv.nx, s.gv.ny, s.gv.nz, q->stream);
@@ -440,6 +442,7 @@ int init_shot(sp_queue *q, Shot &s) {
     return SP_OK;
 }
 
+// Launch the copy of a finished shot's field; the caller waits for the stream.
 int finish_shot(sp_queue *q, Shot &s) {
     if (q->fake || !s.d.final_out) return SP_OK;
     float *scale = nullptr;
@@ -450,7 +453,6 @@ int finish_shot(sp_queue *q, Shot &s) {
     hipError_t e = sp::launch_unpack(s.g.dtype, static_cast<char *>(s.cur) + s.g.origin * s.g.elem_bytes,
                                      scale, s.d.final_out, s.g.pitch_x, s.g.pitch_x * s.g.pitch_y,
                                      s.g.nx, s.g.ny, s.g.nz, q->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(q->stream);
     if (e != hipSuccess) return fail(SP_EDEVICE, "queue: final field: %s", hipGetErrorString(e));
     return SP_OK;
 }
@@ -527,11 +529,27 @@ void worker_main(sp_queue *q) {
         {
             std::lock_guard<std::mutex> lk(q->mu);
             std::vector<uint64_t> still;
+            // the final fields of all shots that end here, and one wait for them
+            bool wait = false;
+            for (uint64_t id : q->active) {
+                Shot &s = q->shots[id];
+                if (err || s.blown || s.step + k < s.d.nsteps) continue;
+                if (k % 2) std::swap(s.cur, s.prev);
+                s.step += k;
+                s.error = finish_shot(q, s);
+                wait = true;
+            }
+            if (wait && !q->fake) {
+                const hipError_t e = hipStreamSynchronize(q->stream);
+                if (e != hipSuccess) err = fail(SP_EDEVICE, "queue: final field: %s", hipGetErrorString(e));
+            }
             for (uint64_t id : q->active) {
                 Shot &s = q->shots[id];
                 if (err) {
                     s.state = SP_SHOT_FAILED;
                     s.error = err;
+                } else if (s.step >= s.d.nsteps) {
+                    s.state = s.error ? SP_SHOT_FAILED : SP_SHOT_DONE;
                 } else {
                     s.step += k;
                     if (k % 2) std::swap(s.cur, s.prev);
@@ -540,10 +558,6 @@ void worker_main(sp_queue *q) {
                         // (no shot reads another's memory)
                         s.state = SP_SHOT_FAILED;
                         s.error = SP_ENUMERIC;
-                    } else if (s.step >= s.d.nsteps) {
-                        const int e = finish_shot(q, s);
-                        s.state = e ? SP_SHOT_FAILED : SP_SHOT_DONE;
-                        s.error = e;
                     }
                 }
                 if (s.state == SP_SHOT_RUNNING) {

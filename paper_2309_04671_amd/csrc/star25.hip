@@ -1258,6 +1258,11 @@ __global__ void __launch_bounds__(512) k_sum(const double *partial, int n, doubl
 
 template <typename T> __global__ void k_record(const RecArgs a) { record_block<T>(a, (int)blockIdx.x); }
 
+// One store per flag, across the bus (a copy per shot and chunk was 4.6 us).
+__global__ void k_gather_flags(const FlagSet f, int n, uint32_t *out) {
+    if ((int)threadIdx.x < n) out[threadIdx.x] = *f.flag[threadIdx.x];
+}
+
 template <typename T>
 __global__ void k_record_batch(const RecArgs *__restrict__ recs, const int2 *__restrict__ rmap,
                                int total) {
@@ -1663,6 +1668,13 @@ hipError_t launch_sweep_batch(int mode, int dtype, const TileCfg &t, const Sweep
         case SP_BF16: return launch_batch_cfg<__bf16>(mode, t, args, table, nblk, s);
         default: return hipErrorInvalidValue;
     }
+}
+
+hipError_t launch_gather_flags(const FlagSet &f, int n, uint32_t *out, hipStream_t s) {
+    if (n <= 0) return hipSuccess;
+    if (n > MAX_FLAGS) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_gather_flags, dim3(1), dim3(MAX_FLAGS), 0, s, f, n, out);
+    return hipGetLastError();
 }
 
 hipError_t launch_record_batch(int dtype, const RecArgs *recs, const int2 *rmap, int total,
