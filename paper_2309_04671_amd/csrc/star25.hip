@@ -1509,7 +1509,7 @@ TileCfg fastest_sweep(const SweepRate *r, int n, int nx, int ny, int nz, int byt
     return best;
 }
 
-// Rates of fastest_sweep: FP32 leapfrog, FP32 apply, 16-bit leapfrog.
+// Rates of fastest_sweep: FP32 leapfrog, FP32 apply, 16-bit leapfrog, energy.
 constexpr SweepRate WAVE32[3] = {
     {128, 32, 2, 1, {{1.46, 1.43, 1.89, 0.04}, {2.02, 1.66, 2.13, 2.34}, {2.25, 1.50, 6.00, 3.00}}},
     {256, 16, 2, 1, {{1.61, 1.47, 0.81, 0.01}, {1.92, 1.92, 1.76, 0.10}, {2.14, 1.47, 6.00, 2.92}}},
@@ -1521,6 +1521,9 @@ constexpr SweepRate APPLY32[3] = {
 constexpr SweepRate WAVE16[2] = {
     {128, 16, 2, 3, {{0.80, 1.27, 1.12, 1.48}, {1.13, 2.62, 0.49, 0.75}, {0.90, 2.40, 0.70, 1.00}}},
     {64, 16, 1, 4, {{0.32, 0.81, 0.92, 2.33}, {0.44, 1.50, 1.15, 1.89}, {0.48, 2.00, 0.70, 1.00}}}};
+constexpr SweepRate ENERGY[2] = {
+    {128, 32, 2, 1, {{1.42, 1.42, 2.82, 0.05}, {2.26, 1.92, 2.16, 0.61}, {2.46, 2.46, 6.00, 3.00}}},
+    {64, 16, 1, 3, {{0.41, 0.90, 3.58, 0.01}, {0.62, 1.45, 0.52, 1.33}, {0.58, 1.75, 1.83, 0.00}}}};
 
 TileCfg choose_tiles_batch(const std::vector<sp_grid> &grids, int max_zchunk, int64_t max_blocks) {
     const bool f32 = grids[0].dtype == SP_F32;
@@ -1559,11 +1562,22 @@ TileCfg choose_tiles(int nx, int ny, int nz, int dtype, int mode) {
         if (dtype == SP_F32 && mode == MODE_WAVE && t.tx == 256 && t.zchunk <= 48) t.ry = 1;
         return t;
     }
+    // The energy sweep of fields past the L2 caches, unless that takes more
+    // partial sums than half of sp_energy_noalloc's scratch holds.  On 35
+    // grids outside its fit 3 % faster than the tiles below, which small grids
+    // keep (480x346x516 228 -> 226 us, 199x299x129 33.6 -> 30.2, 384x200x466
+    // 88 -> 92, the others between).
+    if (mode == MODE_ENERGY && (double)nx * ny * nz * 12 >= 36e6) {
+        const TileCfg t = fastest_sweep(ENERGY, 2, nx, ny, nz, 12);
+        if ((int64_t)((nx + t.tx - 1) / t.tx) * ((ny + t.ty - 1) / t.ty) * ((nz + t.zchunk - 1) / t.zchunk) <= 32768)
+            return t;
+    }
     // The other sweeps take the widest tile that does not waste more than a
     // quarter of its columns on the ragged x edge, and the z-split whose
     // blocks (`want` of them at a time: one 512-thread or two 256-thread
     // blocks per CU) fill the GPU best:
-    //  * gradient and energy: 512-thread 256x16x2 tiles, one block per CU;
+    //  * gradient and small energy sweeps: 512-thread 256x16x2 tiles, one
+    //    block per CU;
     //  * the absorbing-layer mode: one row per thread in 512-thread 256x8x1
     //    tiles, 64x16x1 or 32x32x1 for narrow boxes (the x slabs);
     //  * the fused adjoint sweep (two stencil fields per thread): one row per
