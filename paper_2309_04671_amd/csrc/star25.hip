@@ -26,7 +26,7 @@
 //  * FP16/BF16 storage: value = stored * 2^e per 16-plane slab.  Each step
 //    chooses the output slab exponent a priori from the maxima of its inputs
 //    (so the stored magnitude stays <= 2^15), and reduces the output maxima
-//    for the next step with one atomic max per wave and slab.
+//    for the next step with one atomic max per block and slab.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
