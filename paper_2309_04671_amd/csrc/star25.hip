@@ -1509,7 +1509,8 @@ TileCfg fastest_sweep(const SweepRate *r, int n, int nx, int ny, int nz, int byt
     return best;
 }
 
-// Rates of fastest_sweep: FP32 leapfrog, FP32 apply, 16-bit leapfrog, energy.
+// Rates of fastest_sweep: FP32 leapfrog, FP32 apply, 16-bit leapfrog, energy,
+// fused adjoint.
 constexpr SweepRate WAVE32[3] = {
     {128, 32, 2, 1, {{1.46, 1.43, 1.89, 0.04}, {2.02, 1.66, 2.13, 2.34}, {2.25, 1.50, 6.00, 3.00}}},
     {256, 16, 2, 1, {{1.61, 1.47, 0.81, 0.01}, {1.92, 1.92, 1.76, 0.10}, {2.14, 1.47, 6.00, 2.92}}},
@@ -1524,6 +1525,9 @@ constexpr SweepRate WAVE16[2] = {
 constexpr SweepRate ENERGY[2] = {
     {128, 32, 2, 1, {{1.42, 1.42, 2.82, 0.05}, {2.26, 1.92, 2.16, 0.61}, {2.46, 2.46, 6.00, 3.00}}},
     {64, 16, 1, 3, {{0.41, 0.90, 3.58, 0.01}, {0.62, 1.45, 0.52, 1.33}, {0.58, 1.75, 1.83, 0.00}}}};
+constexpr SweepRate ADJ32[2] = {
+    {128, 16, 1, 1, {{2.41, 2.41, 1.53, 0.12}, {3.01, 2.08, 0.87, 0.27}, {2.78, 2.78, 4.03, 0.03}}},
+    {64, 16, 1, 2, {{1.56, 2.28, 1.16, 0.05}, {1.90, 3.49, 0.42, 0.07}, {2.08, 3.98, 0.07, 0.19}}}};
 
 TileCfg choose_tiles_batch(const std::vector<sp_grid> &grids, int max_zchunk, int64_t max_blocks) {
     const bool f32 = grids[0].dtype == SP_F32;
@@ -1562,6 +1566,13 @@ TileCfg choose_tiles(int nx, int ny, int nz, int dtype, int mode) {
         if (dtype == SP_F32 && mode == MODE_WAVE && t.tx == 256 && t.zchunk <= 48) t.ry = 1;
         return t;
     }
+    // The fused adjoint sweep (two stencil fields per thread): one row per
+    // thread in 512-thread 128x16x1 tiles or two 64x16x1 tiles to a CU (256^3 x
+    // 1000 forward plus backward: 0.220 s against 0.224 on 256x8x1 tiles).  The
+    // narrow tiles wherever a row of wide ones wasted a quarter, and rounds of
+    // 256 blocks only, had cost 4 % on average over 60 grids and 16 % at most
+    // (84x115x121 15.0 -> 12.9 us per step, 201x197x131 51.5 -> 46.1).
+    if (mode == MODE_ADJ) return fastest_sweep(ADJ32, 2, nx, ny, nz, 36);
     // The energy sweep of fields past the L2 caches, unless that takes more
     // partial sums than half of sp_energy_noalloc's scratch holds.  On 35
     // grids outside its fit 3 % faster than the tiles below, which small grids
@@ -1579,18 +1590,13 @@ TileCfg choose_tiles(int nx, int ny, int nz, int dtype, int mode) {
     //  * gradient and small energy sweeps: 512-thread 256x16x2 tiles, one
     //    block per CU;
     //  * the absorbing-layer mode: one row per thread in 512-thread 256x8x1
-    //    tiles, 64x16x1 or 32x32x1 for narrow boxes (the x slabs);
-    //  * the fused adjoint sweep (two stencil fields per thread): one row per
-    //    thread in 512-thread 128x16x1 tiles, 64x16x1 for narrow grids (256^3
-    //    x 1000 forward plus backward: 0.220 s against 0.224 on 256x8x1 and
-    //    0.233 on 64x16x1 tiles).
+    //    tiles, 64x16x1 or 32x32x1 for narrow boxes (the x slabs).
     struct Cand {
         int tx, ty, ry, want;
     };
     static const Cand c32[3] = {{256, 16, 2, 256}, {128, 16, 2, 512}, {64, 16, 1, 512}};
     static const Cand cpm[3] = {{256, 8, 1, 256}, {64, 16, 1, 512}, {32, 32, 1, 512}};
-    static const Cand cad[3] = {{128, 16, 1, 256}, {64, 16, 1, 512}, {64, 16, 1, 512}};
-    const Cand *cand = mode == MODE_PML ? cpm : mode == MODE_ADJ ? cad : c32;
+    const Cand *cand = mode == MODE_PML ? cpm : c32;
     TileCfg t;
     int want = 256;
     for (int c = 0; c < 3; ++c) {
